@@ -24,7 +24,8 @@
 //   * K and V^T tiles are double-buffered in LDS and fetched one step ahead through
 //     registers with raw buffer loads (keys past the end read as zeros, no branches);
 //     rows past dh and keys past Nk are zero, so padding adds nothing.
-// fp32 path: one thread per query, keys staged in LDS (parity mode).
+// fp32 path (v_mfma_f32_16x16x4_f32): the same online softmax in fp32 throughout, described
+// at its kernel.
 #include "sf_device.h"
 
 namespace sf {
@@ -1015,6 +1016,225 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_dma72x2_kernel(AttnArgs a) {
 }
 
 // ------------------------------------------------------------------ fp32
+// e^x for x <= 0 (or NaN) in fp32: x log2 e is split into its rounded product hi and the
+// remainder lo (from the fused product and the next bits of log2 e), so that
+// e^x = 2^hi (1 + lo ln 2) with the hardware's 2^hi (about 1 ulp). Below -200 the result
+// is zero either way; the select keeps lo finite there, for masked keys (-inf), and
+// leaves a NaN alone.
+__device__ __forceinline__ float exp_neg(float x) {
+  constexpr float kL = 1.44269502f, kLlo = 1.92596299e-8f, kLn2 = 0.693147182f;
+  x = x < -200.0f ? -200.0f : x;
+  const float hi = x * kL;
+  const float lo = __builtin_fmaf(x, kLlo, __builtin_fmaf(x, kL, -hi));
+  const float e = __builtin_amdgcn_exp2f(hi);
+  return __builtin_fmaf(e, lo * kLn2, e);
+}
+
+// fp32 attention on the matrix cores (v_mfma_f32_16x16x4_f32, exact fp32 products and
+// sums). A workgroup owns 64 queries of one (row, head), 16 per wavefront, and steps over
+// 32 keys at a time:
+//  * scores transposed, S^T = K Q^T: lane (l16, g) (g = lane / 16) holds query l16 and
+//    keys 4 g .. 4 g + 3 of every 16-key block, so the softmax is lane-local but for two
+//    exchanges of the step max (lanes xor 16, 32);
+//  * an MFMA contracts four values, one per g, and a lane feeds it element e of a
+//    16-byte chunk it read whole: chunk 4 kk + g of its K row (and of its query), so MFMA
+//    (kk, e) sums the dims 16 kk + 4 g + e. In O^T = V^T P^T the same holds for keys: the
+//    lane's four probabilities are the B operands as they stand and its A operand is the
+//    16-byte chunk of keys 4 g .. 4 g + 3 of a V^T row. No lane moves a value.
+//  * K and V^T tiles go global -> LDS directly, three stages, two steps ahead, as in the
+//    bf16 kernels; dims past dh and keys past Nk read as zeros.
+// The matrix cores bound it (64 fp32 FLOP per cycle and SIMD): 16 queries per wavefront
+// need 32 B/clk of LDS reads per CU, and the small query block spreads short sequences
+// over the chip. 4 rows x 12 heads x 1024 tokens, head dim 64 (12.9 GFLOP): 117 us, 110
+// TFLOP/s of the 154 that a large fp32 matrix product reaches, against 6940 us with a
+// thread per query; 3 rows x 4 heads x 140 tokens, head dim 48: 9.0 against 775 us.
+// A query's sums depend on its row's keys only, in one fixed order.
+constexpr int kF32Keys = 32;  // keys per step
+constexpr int kF32Q = 64;     // queries per workgroup
+
+// Chunk c of K row r sits at position c ^ f32_kswz(r): all eight bank columns where the
+// row is a multiple of eight chunks, four of them otherwise (two-way conflicts, well below
+// the LDS rate that is needed).
+template <int CP>
+__device__ __forceinline__ int f32_kswz(int r) {
+  if constexpr (CP % 8 == 0)
+    return dma_swz<8>(r);
+  else
+    return r & 3;
+}
+
+template <int DHC>
+__global__ __launch_bounds__(256) void attn_f32_mfma_kernel(AttnArgs a) {
+  constexpr int CP = DHC * 4;                    // 16-byte chunks per K row
+  constexpr int KCH = kF32Keys * CP;             // K chunks per stage
+  constexpr int VCP = kF32Keys / 4;              // chunks per V^T row
+  constexpr int VCH = DHC * 16 * VCP;            // V^T chunks per stage
+  constexpr int LPT = (KCH + VCH) / 256;         // loads per thread and step
+  constexpr int NKB = kF32Keys / 16;
+  static_assert(KCH % 64 == 0 && (KCH + VCH) % 256 == 0, "whole wavefronts of chunks");
+  __shared__ __attribute__((aligned(16))) char st0[(KCH + VCH) * 16];
+  __shared__ __attribute__((aligned(16))) char st1[(KCH + VCH) * 16];
+  __shared__ __attribute__((aligned(16))) char st2[(KCH + VCH) * 16];
+  auto stage = [&](auto s) -> char* {
+    constexpr int S = decltype(s)::value % kAttnStages;
+    if constexpr (S == 0) return st0;
+    else if constexpr (S == 1) return st1;
+    else return st2;
+  };
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, g = lane >> 4;
+  const int nqb = (a.Nq + kF32Q - 1) / kF32Q;
+  const int T = nqb * a.heads * a.rows;
+  const int xcd = blockIdx.x % 8, local = blockIdx.x / 8;
+  const int base = T / 8, rem = T % 8;
+  const int logical = xcd * base + min(xcd, rem) + local;
+  const int qblk = logical % nqb;
+  const int rh = logical / nqb;
+  const int head = rh % a.heads, r = rh / a.heads;
+  const int dh = a.dh;
+  const size_t bh = (size_t)r * a.heads + head;
+  const size_t kr = a.kv_map ? (size_t)a.kv_map[r] : (size_t)r;  // the row whose keys and values r reads
+  const float* Q = (const float*)a.q + bh * a.Nq * dh;
+  const float* Kg = (const float*)a.k + kr * a.k_rs + (size_t)head * a.k_ld * dh;
+  const float* Vt = (const float*)a.vT + kr * a.v_rs + (size_t)head * dh * a.ldv;
+  const int qi = qblk * kF32Q + wave * 16 + l16;
+
+  f32x4 qf[DHC];
+  const __amdgpu_buffer_rsrc_t q_src = buffer_rsrc(Q, (uint32_t)a.Nq * dh * 4);
+#pragma unroll
+  for (int kk = 0; kk < DHC; ++kk) {
+    const int d0 = kk * 16 + g * 4;
+    qf[kk] = __builtin_bit_cast(f32x4, buffer_load16(q_src, (qi < a.Nq && d0 < dh) ? (qi * dh + d0) * 4 : kOffOOB));
+    qf[kk] *= a.scale;
+  }
+
+  int goff[LPT];
+#pragma unroll
+  for (int i = 0; i < LPT; ++i) {
+    const int p = i * 256 + tid;
+    if (p < KCH) {
+      const int row = p / CP, c = (p % CP) ^ f32_kswz<CP>(row);
+      goff[i] = c * 4 < dh ? (row * dh + c * 4) * 4 : kOffOOB;
+    } else {
+      const int pv = p - KCH, row = pv / VCP, c = (pv % VCP) ^ dma_swz<8>(row);
+      goff[i] = row < dh ? (row * a.ldv + c * 4) * 4 : kOffOOB;
+    }
+  }
+  auto issue = [&](char* sb, int step) {
+    const int kv0 = step * kF32Keys;
+    const __amdgpu_buffer_rsrc_t k_src =
+        buffer_rsrc(Kg + (size_t)kv0 * dh, (uint32_t)max(a.Nk - kv0, 0) * dh * 4);
+    const __amdgpu_buffer_rsrc_t v_src = buffer_rsrc(Vt + kv0, (uint32_t)max(dh * a.ldv - kv0, 0) * 4);
+#pragma unroll
+    for (int i = 0; i < LPT; ++i)
+      buffer_load16_lds(i * 256 + wave * 64 < KCH ? k_src : v_src, sb + (i * 256 + wave * 64) * 16, goff[i]);
+  };
+
+  f32x4 o[DHC];
+#pragma unroll
+  for (int b = 0; b < DHC; ++b) o[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY, lsum = 0.0f;
+
+  constexpr int kWait = waitcnt_vm_lgkm0<(kAttnStages - 2) * LPT>();
+  auto step = [&](auto s, int it) {
+    constexpr int S = decltype(s)::value;
+    __builtin_amdgcn_s_waitcnt(kWait);
+    bare_barrier();
+    issue(stage(std::integral_constant<int, S + kAttnStages - 1>{}), it + kAttnStages - 1);
+    const char* cur = stage(std::integral_constant<int, S>{});
+    const int kv0 = it * kF32Keys;
+    f32x4 sc[NKB];
+#pragma unroll
+    for (int kb = 0; kb < NKB; ++kb) sc[kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kk = 0; kk < DHC; ++kk) {
+      f32x4 kf[NKB];
+#pragma unroll
+      for (int kb = 0; kb < NKB; ++kb) {
+        const int row = kb * 16 + l16;
+        kf[kb] = *(const f32x4*)(cur + (row * CP + ((kk * 4 + g) ^ f32_kswz<CP>(row))) * 16);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb)
+          sc[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kb][e], qf[kk][e], sc[kb], 0, 0, 0);
+    }
+    if (kv0 + kF32Keys > a.Nk) {
+#pragma unroll
+      for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (kv0 + kb * 16 + g * 4 + e >= a.Nk) sc[kb][e] = -INFINITY;
+    }
+    float tmax = sc[0][0];
+#pragma unroll
+    for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) tmax = fmaxf(tmax, sc[kb][e]);
+    tmax = pair32_max(pair16_max(tmax));
+    if (__any(tmax > m)) {
+      const float mnew = fmaxf(m, tmax);
+      const float alpha = exp_neg(m - mnew);
+      lsum *= alpha;
+#pragma unroll
+      for (int b = 0; b < DHC; ++b) o[b] *= alpha;
+      m = mnew;
+    }
+    f32x4 p[NKB];
+#pragma unroll
+    for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        p[kb][e] = exp_neg(sc[kb][e] - m);
+        lsum += p[kb][e];
+      }
+    const char* vb = cur + KCH * 16;
+#pragma unroll
+    for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+      for (int b0 = 0; b0 < DHC; b0 += 2) {
+        f32x4 vf[2];
+#pragma unroll
+        for (int b = b0; b < DHC && b < b0 + 2; ++b) {
+          const int row = b * 16 + l16;
+          vf[b - b0] = *(const f32x4*)(vb + (row * VCP + ((kb * 4 + g) ^ dma_swz<8>(row))) * 16);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int b = b0; b < DHC && b < b0 + 2; ++b)
+            o[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[b - b0][e], p[kb][e], o[b], 0, 0, 0);
+      }
+  };
+
+  const int nsteps = (a.Nk + kF32Keys - 1) / kF32Keys;
+  issue(stage(std::integral_constant<int, 0>{}), 0);
+  issue(stage(std::integral_constant<int, 1>{}), 1);
+  int it = 0;
+  for (; it + kAttnStages <= nsteps; it += kAttnStages) {
+    step(std::integral_constant<int, 0>{}, it);
+    step(std::integral_constant<int, 1>{}, it + 1);
+    step(std::integral_constant<int, 2>{}, it + 2);
+  }
+  if (it < nsteps) step(std::integral_constant<int, 0>{}, it);
+  if (it + 1 < nsteps) step(std::integral_constant<int, 1>{}, it + 1);
+  // the loads past the last key land before the workgroup's LDS is given up
+  __builtin_amdgcn_s_waitcnt(0);
+
+  lsum = pair32_sum(pair16_sum(lsum));
+  if (qi < a.Nq) {
+    float* O = (float*)a.o + ((size_t)r * a.Nq + qi) * a.D + (size_t)head * dh;
+#pragma unroll
+    for (int b = 0; b < DHC; ++b) {
+      const int d = b * 16 + g * 4;
+      if (d < dh) *(f32x4*)(O + d) = f32x4{o[b][0] / lsum, o[b][1] / lsum, o[b][2] / lsum, o[b][3] / lsum};
+    }
+  }
+}
+
+// The same for operands that the matrix-core kernel cannot load: one thread per query,
+// keys staged in LDS.
 constexpr int kFKV = 32;
 
 template <int DHMAX>
@@ -1067,6 +1287,17 @@ __global__ __launch_bounds__(128) void attn_f32_kernel(AttnArgs a) {
     for (int d = 0; d < DHMAX; ++d)
       if (d < dh) O[d] = o[d] / l;
   }
+}
+
+// The matrix-core kernel moves 16-byte chunks, so it takes pointers on 16-byte
+// boundaries (the library's own always are; a caller's of sf_attention may not be), and
+// its buffer offsets are 32 bits wide.
+static bool f32_mfma_fits(const AttnArgs& a) {
+  const uintptr_t p = (uintptr_t)a.q | (uintptr_t)a.k | (uintptr_t)a.vT | (uintptr_t)a.o;
+  const uint64_t most = (uint64_t)kOffOOBHost;
+  return p % 16 == 0 && a.ldv % 4 == 0 && a.ldv >= (a.Nk + kF32Keys - 1) / kF32Keys * kF32Keys && a.k_rs % 4 == 0 &&
+         a.v_rs % 4 == 0 && (uint64_t)a.Nq * a.dh * 4 < most && (uint64_t)a.Nk * a.dh * 4 < most &&
+         (uint64_t)a.dh * a.ldv * 4 < most;
 }
 
 bool attention_supports(int dh) { return dh >= 8 && dh <= 128 && dh % 8 == 0; }
@@ -1125,6 +1356,19 @@ hipError_t launch_attention(bool use_bf16, const AttnArgs& args, hipStream_t s) 
       case 6: launch_bf16_inst<6, 3>(a, two, s); break;
       case 7: launch_bf16_inst<7, 4>(a, two, s); break;
       case 8: launch_bf16_inst<8, 4>(a, two, s); break;
+      default: return hipErrorInvalidValue;
+    }
+  } else if (f32_mfma_fits(a)) {
+    const dim3 grid(((a.Nq + kF32Q - 1) / kF32Q) * a.heads * a.rows);
+    switch ((a.dh + 15) / 16) {
+      case 1: launch(attn_f32_mfma_kernel<1>, grid, dim3(256), 0, s, a); break;
+      case 2: launch(attn_f32_mfma_kernel<2>, grid, dim3(256), 0, s, a); break;
+      case 3: launch(attn_f32_mfma_kernel<3>, grid, dim3(256), 0, s, a); break;
+      case 4: launch(attn_f32_mfma_kernel<4>, grid, dim3(256), 0, s, a); break;
+      case 5: launch(attn_f32_mfma_kernel<5>, grid, dim3(256), 0, s, a); break;
+      case 6: launch(attn_f32_mfma_kernel<6>, grid, dim3(256), 0, s, a); break;
+      case 7: launch(attn_f32_mfma_kernel<7>, grid, dim3(256), 0, s, a); break;
+      case 8: launch(attn_f32_mfma_kernel<8>, grid, dim3(256), 0, s, a); break;
       default: return hipErrorInvalidValue;
     }
   } else {

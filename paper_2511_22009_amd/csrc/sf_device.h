@@ -90,6 +90,17 @@ __device__ __forceinline__ float pair32_sum(float v) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// The same over the lane pair (l, l ^ 16), by v_permlane16_swap.
+__device__ __forceinline__ float pair16_max(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+__device__ __forceinline__ float pair16_sum(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 // Sums each of 16 per-lane values over the 64 lanes of a wavefront and returns, in
 // lane l, the total of index (l >> 2) & 15 (lanes 4i..4i+3 all hold total i). Butterfly
 // reduce-scatter: four halving exchanges (lane xor 32, 16, 8, 4) then two plain ones

@@ -1,0 +1,76 @@
+"""The fp32 matrix-core kernels alone, at the sizes where their tiles can go wrong, against
+64-bit results on the same inputs. An fp32 sum of n products has a relative error of about
+sqrt(n) 2^-24 (n <= 4096: 4e-6); 1e-6 is what these shapes stay below by a factor of two
+or more, and the bound of one element is forty times that."""
+import numpy as np
+import pytest
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+from gpu_util import host, torch  # noqa: E402
+from helpers import rel_l2  # noqa: E402
+from paper_2511_22009_amd import Model, Precision  # noqa: E402
+
+
+def _attention_model(heads, dh, H, Wd):
+    D = heads * dh
+    cfg = W.Config("attn", C=4, H=H, W=Wd, p=2, D=D, L=1, heads=heads, mlp=D, K=1, schedule="uniform1")
+    return cfg, Model(W.make_blob(cfg), Precision.FP32, 1)
+
+
+def _reference(q, k, v):
+    s = np.einsum("rhqd,rhkd->rhqk", q, k, dtype=np.float64) / np.sqrt(q.shape[-1])
+    p = np.exp(s - s.max(-1, keepdims=True))
+    o = np.einsum("rhqk,rhkd->rhqd", p / p.sum(-1, keepdims=True), v, dtype=np.float64)
+    return o.transpose(0, 2, 1, 3).reshape(q.shape[0], q.shape[2], -1)
+
+
+def _run(m, q, k, v, shift=0):
+    """Attention on device copies of q, k, v; shift > 0 moves every operand that many
+    floats off its 16-byte boundary."""
+    def put(a):
+        buf = torch.empty(a.size + shift, device="cuda")
+        t = buf[shift:].view(a.shape)
+        t.copy_(torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)))
+        return t
+    vt = np.zeros(v.shape[:2] + (v.shape[3], m.info["vt_ld"]), np.float32)
+    vt[..., :v.shape[2]] = v.transpose(0, 1, 3, 2)
+    return host(m.attention(put(q), put(k), put(vt)))
+
+
+@pytest.mark.parametrize("H,Wd", [(2, 2), (6, 10), (8, 8), (6, 22), (10, 26), (20, 28)],
+                         ids=["n1", "n15", "n16", "n33", "n65", "n140"])
+@pytest.mark.parametrize("heads,dh", [(1, 8), (3, 16), (2, 24), (1, 40), (2, 64), (2, 72), (1, 96), (1, 104), (2, 128)])
+def test_attention_fp32(heads, dh, H, Wd):
+    cfg, m = _attention_model(heads, dh, H, Wd)
+    rng = np.random.default_rng([heads, dh, cfg.N])
+    q, k, v = (rng.standard_normal((2, heads, cfg.N, dh)).astype(np.float32) for _ in range(3))
+    q *= 3.0
+    ref = _reference(q, k, v)
+    got = _run(m, q, k, v)
+    assert rel_l2(got, ref) < 1e-6
+    assert np.max(np.abs(got - ref)) < 4e-5 * np.sqrt(np.mean(ref * ref))
+    # operands off their 16-byte boundary take the general kernel: the same result within
+    # the same bound
+    assert rel_l2(_run(m, q, k, v, shift=1), ref) < 1e-6
+    # each row alone gives the bits it has in the batch
+    np.testing.assert_array_equal(_run(m, q[1:], k[1:], v[1:])[0], got[1])
+    m.close()
+
+
+def test_attention_fp32_score_levels_and_nan():
+    """Scores far above, far below and moving through the row (the running max rises at
+    late keys), and a NaN key: its head's outputs are NaN, the other head's are not."""
+    cfg, m = _attention_model(2, 48, 20, 28)
+    rng = np.random.default_rng(5)
+    q, k, v = (rng.standard_normal((1, 2, cfg.N, 48)).astype(np.float32) for _ in range(3))
+    q[..., 0], k[..., 0] = 40.0, np.linspace(-60.0, 60.0, cfg.N)  # scores from -350 to 350
+    ref = _reference(q, k, v)
+    # a score of 350 carries a rounding of about 350 2^-24 sqrt(48) = 1.4e-4 into its exponent
+    assert rel_l2(_run(m, q, k, v), ref) < 1.5e-4
+    k[0, 1, 70, 3] = np.nan
+    got = _run(m, q, k, v)
+    assert np.isnan(got[0, :, 48:]).all() and np.isfinite(got[0, :, :48]).all()
+    m.close()
