@@ -17,7 +17,7 @@
 // registers while the current one feeds the matrix cores. The MFMAs take the weight
 // fragment as the first operand, so each lane ends up holding four adjacent output
 // columns of one row, which the epilogues move in 8- and 16-byte pieces. fp32 path:
-// LDS-tiled FMA GEMM (exact fp32 arithmetic for the parity mode).
+// v_mfma_f32_16x16x4_f32 on directly staged tiles.
 #include <cmath>
 
 #include "sf_device.h"
@@ -49,41 +49,6 @@ __device__ __forceinline__ bool tile_live(const GemmArgs& a, int m0) {
   for (int r = r0; r <= r1; ++r)
     if (a.row_live[r]) return true;
   return false;
-}
-
-template <EpiKind KIND, typename OT>
-__device__ __forceinline__ void epilogue(const GemmArgs& a, int m, int n, float acc) {
-  const float val = acc + a.bias[n];
-  if constexpr (KIND == EPI_QKV || KIND == EPI_KVX) {
-    const int part = (int)fdiv((uint32_t)n, a.div_D);
-    const int rem = n - part * a.D;
-    const int head = (int)fdiv((uint32_t)rem, a.div_dh);
-    const int d = rem - head * a.dh;
-    const int r0 = (int)fdiv((uint32_t)m, a.div_ntok);
-    const int tok = m - r0 * a.ntok;
-    int which, r;
-    qkv_dest<KIND>(a, part, r0, which, r);
-    const size_t bh = (size_t)r * a.heads + head;
-    // Destination picked with selects, not a three-way branch: this compiler lowered
-    // the divergent if / else-if / else form to code that stored the v part through
-    // the k pointer.
-    const size_t i_qk = (bh * a.ntok + tok) * a.dh + d;
-    const size_t i_v = (bh * a.dh + d) * a.ldv + (a.vperm ? vt_pos(tok) : tok);
-    OT* const p_qk = (OT*)(which == 0 ? a.q : a.k);
-    OT* const dst = which >= 2 ? (OT*)a.vT + i_v : p_qk + i_qk;
-    *dst = from_f32<OT>(val);
-  } else if constexpr (KIND == EPI_RES_GATE || KIND == EPI_RES_GATE_MLP) {
-    const int r = (int)fdiv((uint32_t)m, a.div_ntok);
-    const int slot = r < a.n_slots ? r : r - a.n_slots;
-    const float g = a.table[(size_t)slot * a.ldt + a.gate_off + n];
-    float* hp = a.h + (size_t)m * a.ldh + n;
-    *hp = *hp + g * val;
-  } else if constexpr (KIND == EPI_GELU) {
-    ((OT*)a.out)[(size_t)m * a.ldo + n] = from_f32<OT>(gelu_tanh(val));
-  } else {
-    float* hp = a.h + (size_t)m * a.ldh + n;
-    *hp = *hp + val;
-  }
 }
 
 // ------------------------------------------------------------------ bf16 / MFMA
@@ -959,57 +924,192 @@ __global__ __launch_bounds__(WM * WN * KSPLIT * 64) void gemm_bf16_dma_kernel(Ge
   }
 }
 
-// ------------------------------------------------------------------ fp32 / FMA
-constexpr int kFT = 64;   // tile edge
-constexpr int kFK = 16;   // K slice
-
+// ------------------------------------------------------------------ fp32 / MFMA
+//
+// fp32 projections on v_mfma_f32_16x16x4_f32 (exact fp32 products and sums). Operand
+// slices of 32 columns go global -> LDS directly into a ring of three stages, two slices
+// ahead, in the layout of the bf16 kernel above (rows of eight 16-byte chunks, swizzled).
+// An MFMA contracts four values, one per lane group g = lane / 16; a lane reads whole
+// chunks (chunk 4 kk + g of its row) and feeds MFMA (kk, e) their element e, so that MFMA
+// sums columns 16 kk + 4 g + e of the slice. Every tile shape sums K in this one order, so
+// the choice of a tile, by M too, changes no result bit.
+//
+// The weights are the first operand: lane (l16, g) ends up with four adjacent output
+// columns 4 g .. 4 g + 3 of row l16 of each 16 x 16 block, which leave as 16-byte accesses
+// straight from registers (single stores for the transposed v, whose lanes hold adjacent
+// tokens). The matrix cores bound it: 64 FLOP per cycle and SIMD against 16 B/clk of
+// operand loads per CU for the 64 x 64 tile. 4096 x 768 x 3072: 152 us, 127 TFLOP/s of the
+// 154 that a large product reaches, against 396 us for a 64 x 64 tile of vector FMAs;
+// 420 x 192 x 768: 7.0 against 77 us.
 template <EpiKind KIND>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
-  __shared__ float As[kFK][kFT + 4];
-  __shared__ float Bs[kFK][kFT + 4];
+__device__ __forceinline__ void f32_epilogue4(const GemmArgs& a, int m, int n, const f32x4& acc) {
+  const f32x4 b = *(const f32x4*)(a.bias + n);
+  f32x4 v;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = acc[e] + b[e];
+  if constexpr (KIND == EPI_QKV || KIND == EPI_KVX) {
+    // the four columns belong to one head (head widths are multiples of eight)
+    const int part = (int)fdiv((uint32_t)n, a.div_D);
+    const int rem = n - part * a.D;
+    const int head = (int)fdiv((uint32_t)rem, a.div_dh);
+    const int d = rem - head * a.dh;
+    const int r0 = (int)fdiv((uint32_t)m, a.div_ntok);
+    const int tok = m - r0 * a.ntok;
+    int which, r;
+    qkv_dest<KIND>(a, part, r0, which, r);
+    const size_t bh = (size_t)r * a.heads + head;
+    if (which < 2) *(f32x4*)((float*)(which == 0 ? a.q : a.k) + (bh * a.ntok + tok) * a.dh + d) = v;
+    if (which >= 2) {
+      float* vt = (float*)a.vT + (bh * a.dh + d) * a.ldv + tok;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) vt[(size_t)e * a.ldv] = v[e];
+    }
+  } else if constexpr (KIND == EPI_GELU) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = gelu_tanh(v[e]);
+    *(f32x4*)((float*)a.out + (size_t)m * a.ldo + n) = v;
+  } else {
+    f32x4* hp = (f32x4*)(a.h + (size_t)m * a.ldh + n);
+    f32x4 h = *hp;
+    if constexpr (KIND == EPI_RES_GATE || KIND == EPI_RES_GATE_MLP) {
+      const int r = (int)fdiv((uint32_t)m, a.div_ntok);
+      const int slot = r < a.n_slots ? r : r - a.n_slots;
+      const f32x4 g = *(const f32x4*)(a.table + (size_t)slot * a.ldt + a.gate_off + n);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) h[e] += g[e] * v[e];
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) h[e] += v[e];
+    }
+    *hp = h;
+  }
+}
+
+template <int BM, int BN, int WM, int WN, EpiKind KIND>
+__global__ __launch_bounds__(WM * WN * 64) void gemm_f32_kernel(GemmArgs a) {
+  constexpr int NT = WM * WN * 64, BK = 32, CPR = 8, STAGES = 3;
+  constexpr int TM = BM / WM / 16, TN = BN / WN / 16;
+  static_assert(TM * WM * 16 == BM && TN * WN * 16 == BN, "wave grid must tile the block");
+  constexpr int ATOT = BM * CPR, BTOT = BN * CPR;
+  static_assert(ATOT % NT == 0 && BTOT % NT == 0, "whole rounds of chunks per slice");
+  constexpr int ACH = ATOT / NT, BCH = BTOT / NT, LPT = ACH + BCH;
+  __shared__ __attribute__((aligned(16))) char st0[(ATOT + BTOT) * 16];
+  __shared__ __attribute__((aligned(16))) char st1[(ATOT + BTOT) * 16];
+  __shared__ __attribute__((aligned(16))) char st2[(ATOT + BTOT) * 16];
+  auto stage = [&](auto s) -> char* {
+    constexpr int S = decltype(s)::value % STAGES;
+    if constexpr (S == 0) return st0;
+    else if constexpr (S == 1) return st1;
+    else return st2;
+  };
   const int tid = threadIdx.x;
-  const int tx = tid & 15, ty = tid >> 4;
-  const int m0 = blockIdx.y * kFT, n0 = blockIdx.x * kFT;
-  if (!tile_live<KIND, kFT>(a, m0)) return;
-  const float* A = (const float*)a.A;
-  const float* B = (const float*)a.B;
-  float acc[4][4] = {};
-  const int lr = tid >> 2, lk = (tid & 3) * 4;  // loader: row lr, k offset lk
-  for (int k0 = 0; k0 < a.K; k0 += kFK) {
-    {
-      const int gm = m0 + lr, gk = k0 + lk;
-      float4 v = (gm < a.M && gk < a.K) ? *(const float4*)(A + (size_t)gm * a.lda + gk) : make_float4(0, 0, 0, 0);
-      As[lk + 0][lr] = v.x; As[lk + 1][lr] = v.y; As[lk + 2][lr] = v.z; As[lk + 3][lr] = v.w;
-      const int gn = n0 + lr;
-      float4 w = (gn < a.N && gk < a.K) ? *(const float4*)(B + (size_t)gn * a.ldb + gk) : make_float4(0, 0, 0, 0);
-      Bs[lk + 0][lr] = w.x; Bs[lk + 1][lr] = w.y; Bs[lk + 2][lr] = w.z; Bs[lk + 3][lr] = w.w;
-    }
-    __syncthreads();
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const int l16 = lane & 15, g = lane >> 4;
+  int mt, nt;
+  tile_coords((a.M + BM - 1) / BM, (a.N + BN - 1) / BN, mt, nt);
+  const int m0 = mt * BM, n0 = nt * BN;
+  if (!tile_live<KIND, BM>(a, m0)) return;  // uniform across the workgroup
+
+  // load i of a thread fills chunk position i * NT + tid of the A (or B) part of a stage.
+  // The resources are based at the tile's first row and the slice's first column, so 32-bit
+  // offsets reach any operand; rows past M or N lie past the resource's end
+  int a_off[ACH], b_off[BCH], a_kc[ACH], b_kc[BCH];
 #pragma unroll
-    for (int kk = 0; kk < kFK; ++kk) {
-      float av[4], bv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) av[i] = As[kk][ty + 16 * i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) bv[j] = Bs[kk][tx + 16 * j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += av[i] * bv[j];
-    }
-    __syncthreads();
+  for (int i = 0; i < ACH; ++i) {
+    const int p = tid + i * NT, row = p / CPR;
+    a_kc[i] = ((p % CPR) ^ dma_swz<CPR>(row)) * 4;
+    a_off[i] = (row * a.lda + a_kc[i]) * 4;
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + ty + 16 * i;
+  for (int i = 0; i < BCH; ++i) {
+    const int p = tid + i * NT, row = p / CPR;
+    b_kc[i] = ((p % CPR) ^ dma_swz<CPR>(row)) * 4;
+    b_off[i] = (row * a.ldb + b_kc[i]) * 4;
+  }
+  const float* const A0 = (const float*)a.A + (size_t)m0 * a.lda;
+  const float* const B0 = (const float*)a.B + (size_t)n0 * a.ldb;
+  const int a_rows = min(a.M - m0, BM), b_rows = min(a.N - n0, BN);
+  auto issue = [&](char* sb, int kt) {
+    const int k0 = kt * BK;
+    const bool live = k0 < a.K;
+    const __amdgpu_buffer_rsrc_t ra = buffer_rsrc(A0 + k0, live ? (uint32_t)(a_rows * a.lda - k0) * 4 : 0u);
+    const __amdgpu_buffer_rsrc_t rb = buffer_rsrc(B0 + k0, live ? (uint32_t)(b_rows * a.ldb - k0) * 4 : 0u);
+#pragma unroll
+    for (int i = 0; i < ACH; ++i)
+      buffer_load16_lds(ra, sb + (i * NT + wave * 64) * 16, k0 + a_kc[i] < a.K ? a_off[i] : kOffOOB);
+#pragma unroll
+    for (int i = 0; i < BCH; ++i)
+      buffer_load16_lds(rb, sb + (ATOT + i * NT + wave * 64) * 16, k0 + b_kc[i] < a.K ? b_off[i] : kOffOOB);
+  };
+
+  f32x4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int sw = dma_swz<CPR>(l16);  // row blocks are 16 apart: every row of a lane shares it
+  const int a_row = (wm * TM * 16 + l16) * CPR, b_row = ATOT + (wn * TN * 16 + l16) * CPR;
+
+  constexpr int kWait = waitcnt_vm_lgkm0<(STAGES - 2) * LPT>();
+  auto step = [&](auto s, int kt) {
+    constexpr int S = decltype(s)::value;
+    __builtin_amdgcn_s_waitcnt(kWait);
+    bare_barrier();
+    issue(stage(std::integral_constant<int, S + STAGES - 1>{}), kt + STAGES - 1);
+    const char* cur = stage(std::integral_constant<int, S>{});
+    f32x4 af[2][TM], bf[2][TN];
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) af[kk][i] = *(const f32x4*)(cur + (a_row + i * 16 * CPR + ((kk * 4 + g) ^ sw)) * 16);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) bf[kk][j] = *(const f32x4*)(cur + (b_row + j * 16 * CPR + ((kk * 4 + g) ^ sw)) * 16);
+    }
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bf[kk][j][e], af[kk][i][e], acc[i][j], 0, 0, 0);
+  };
+
+  const int nk = (a.K + BK - 1) / BK;
+  issue(stage(std::integral_constant<int, 0>{}), 0);
+  issue(stage(std::integral_constant<int, 1>{}), 1);
+  int kt = 0;
+  for (; kt + STAGES <= nk; kt += STAGES) {
+    step(std::integral_constant<int, 0>{}, kt);
+    step(std::integral_constant<int, 1>{}, kt + 1);
+    step(std::integral_constant<int, 2>{}, kt + 2);
+  }
+  if (kt < nk) step(std::integral_constant<int, 0>{}, kt);
+  if (kt + 1 < nk) step(std::integral_constant<int, 1>{}, kt + 1);
+  __builtin_amdgcn_s_waitcnt(0);  // the loads past K land before the LDS is given up
+
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    const int m = m0 + (wm * TM + i) * 16 + l16;
     if (m >= a.M) continue;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx + 16 * j;
-      if (n < a.N) epilogue<KIND, float>(a, m, n, acc[i][j]);
+    for (int j = 0; j < TN; ++j) {
+      const int n = n0 + (wn * TN + j) * 16 + g * 4;
+      if (n < a.N) f32_epilogue4<KIND>(a, m, n, acc[i][j]);
     }
   }
 }
+
+// fp32 tiles (BM x BN, wave grid): 64 x 64 where it gives at least two workgroups per CU,
+// 32 x 32 below, where it spreads the rows over more of the chip (4096 x 3072 x 768: 158 us
+// with 64 x 64, 171 with 32 x 32; 1024 x 768 x 768: 18.9 and 15.1; 420 x 192 x 768: 17.3
+// and 7.0). 128 x 64 and 128 x 128 tiles were no faster (149 and 156 us for the first, 54
+// us for 4096 x 768 x 768 against 47).
+#define SF_GEMM_F32_TILES(X) \
+  X(0, 64, 64, 2, 2)         \
+  X(1, 32, 32, 2, 2)
 
 // Tile shapes (BM x BN x BK, wave grid WM x WN, K split). Per-wave tiles are 64x64,
 // 64x96 or 32x96; with a K split of 2 a second set of wavefronts takes the second half
@@ -1079,12 +1179,31 @@ int choose_gemm_tile(int M, int N, int K) {
   return 0;
 }
 
+int choose_gemm_f32_tile(int M, int N) {
+  auto tiles = [&](int bm, int bn) { return (size_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  return tiles(64, 64) >= 512 ? 0 : 1;
+}
+
+template <EpiKind KIND>
+static hipError_t launch_f32_tile(int tile, const GemmArgs& a, hipStream_t s) {
+  switch (tile) {
+#define SF_F32_TILE_CASE(id, bm, bn, wm, wn)                                                  \
+  case id:                                                                                    \
+    launch((gemm_f32_kernel<bm, bn, wm, wn, KIND>),                                           \
+           dim3(((a.N + bn - 1) / bn) * ((a.M + bm - 1) / bm)), dim3(wm * wn * 64), 0, s, a); \
+    break;
+    SF_GEMM_F32_TILES(SF_F32_TILE_CASE)
+#undef SF_F32_TILE_CASE
+    default:
+      return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
 template <EpiKind KIND>
 static hipError_t launch_kind(bool use_bf16, int tile, const GemmArgs& a, hipStream_t s) {
   if (use_bf16) return launch_bf16_tile<KIND>(tile < 0 ? choose_gemm_tile(a.M, a.N, a.K) : tile, a, s);
-  dim3 grid((a.N + kFT - 1) / kFT, (a.M + kFT - 1) / kFT);
-  launch(gemm_f32_kernel<KIND>, grid, dim3(256), 0, s, a);
-  return hipGetLastError();
+  return launch_f32_tile<KIND>(tile < 0 ? choose_gemm_f32_tile(a.M, a.N) : tile, a, s);
 }
 
 hipError_t launch_gemm_tile(bool use_bf16, int tile, EpiKind kind, const GemmArgs& a, hipStream_t s) {

@@ -74,3 +74,23 @@ def test_attention_fp32_score_levels_and_nan():
     got = _run(m, q, k, v)
     assert np.isnan(got[0, :, 48:]).all() and np.isfinite(got[0, :, :48]).all()
     m.close()
+
+
+def test_gemm_fp32_tiles_and_ragged_k():
+    """Widths that are multiples of neither fp32 tile nor of the 32-wide K slice (K 200,
+    1032; N 200, 600, 1032). 64 rows of 84 tokens take 64 x 64 tiles for the QKV and MLP
+    up-projections and 32 x 32 tiles for the other two, one row 32 x 32 tiles throughout:
+    against the oracle (sums of at most 1032 products: 2e-6), and the same bits."""
+    import oracle
+    cfg = W.Config("odd", C=4, H=14, W=24, p=2, D=200, L=1, heads=5, mlp=1032)
+    blob = W.make_blob(cfg, init="tsens")
+    m = Model(blob, Precision.FP32, 64)
+    x = W.latents(cfg, 64, seed=7)
+    t = np.random.default_rng(8).uniform(0.0, 1.0, 64).astype(np.float32)
+    put = lambda a: torch.from_numpy(a).cuda()  # noqa: E731
+    got = host(m.velocity(put(x), t))
+    om = oracle.load_blob(blob)
+    for k in (0, 31, 63):
+        assert rel_l2(got[k], oracle.forward_one(om, x[k], t[k], dtype=np.float64)) < 2e-6
+        np.testing.assert_array_equal(host(m.velocity(put(x[k:k + 1]), t[k:k + 1]))[0], got[k])
+    m.close()
