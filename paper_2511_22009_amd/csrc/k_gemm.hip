@@ -9,12 +9,10 @@
 //   KVX      + bias, the cross-attention keys and transposed values of every block at
 //            once (one context entry per network row).
 //
-// bf16 path: v_mfma_f32_32x32x16_bf16 on BM x BN x BK workgroup tiles (BK 64 or 128;
-// table at the end), each wavefront owning a 64x64, 64x96 or 32x96 sub-tile, optionally with
-// the K slice split over two sets of wavefronts; both operand tiles are
-// double-buffered in LDS with a 16-byte row pad so the 16-byte fragment reads of a
-// 32-lane column are free of bank conflicts, and the next K-slice is fetched into
-// registers while the current one feeds the matrix cores. The MFMAs take the weight
+// bf16 path: v_mfma_f32_32x32x16_bf16 on BM x BN workgroup tiles over 64-wide K slices
+// (table and choice at the end), each wavefront owning a 64x64, 64x96, 32x96 or 32x32
+// sub-tile. Operand slices reach LDS directly in a swizzled layout or, for one tile, through
+// registers into a padded one; fragment reads are free of bank conflicts in both. The MFMAs take the weight
 // fragment as the first operand, so each lane ends up holding four adjacent output
 // columns of one row, which the epilogues move in 8- and 16-byte pieces. fp32 path:
 // v_mfma_f32_16x16x4_f32 on directly staged tiles.
@@ -322,6 +320,31 @@ __device__ __forceinline__ void bf16_epilogue(const GemmArgs& a, const f32x16 (&
             *(u32x4*)(vt + (size_t)j * a.ldv) = u32x4{pk(0, 1), pk(2, 3), pk(8, 9), pk(10, 11)};
             *(u32x4*)(vt + (size_t)j * a.ldv + 8) = u32x4{pk(4, 5), pk(6, 7), pk(12, 13), pk(14, 15)};
           }
+        } else if ((a.ntok & 3) == 0 && n + 8 <= a.N) {
+          // token counts that are multiples of 4 but not of 16 (2760 x 2304 x 768 with 920
+          // tokens: 33.9 us with single stores, 20.7 so): four rows from m = 4 i on
+          // are four tokens of one network row from a multiple of 4 on, which the permuted
+          // order keeps adjacent: one 8-byte store per column
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int me = m + 4 * q;
+            if (me >= a.M) break;
+            const int re0 = (int)fdiv((uint32_t)me, a.div_ntok);
+            const int te = me - re0 * a.ntok;
+            int we, re;
+            qkv_dest<KIND>(a, part, re0, we, re);
+            u32x4 rows[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) rows[e] = *(const u32x4*)&Cs[(rb * 16 + 4 * q + e) * CPB + cg * 8];
+            bf16* vt = (bf16*)a.vT + (((size_t)re * a.heads + head) * a.dh + d0) * a.ldv + vt_pos(te);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+              const uint32_t sel = (j & 1) ? 0x07060302u : 0x05040100u;
+              const uint2 w = {__builtin_amdgcn_perm(rows[1][j >> 1], rows[0][j >> 1], sel),
+                               __builtin_amdgcn_perm(rows[3][j >> 1], rows[2][j >> 1], sel)};
+              *(uint2*)(vt + (size_t)j * a.ldv) = w;
+            }
+          }
         } else {
           for (int e = 0; e < 16 && m + e < a.M; ++e) {
             const int me = m + e;
@@ -346,12 +369,11 @@ __device__ __forceinline__ void bf16_epilogue(const GemmArgs& a, const f32x16 (&
 // Block -> tile map. The hardware hands workgroup b to XCD b % 8 and each XCD has its
 // own L2, so each XCD gets a contiguous range of logical tiles; inside it tiles go in
 // groups of GM tile rows, M fastest, so the A rows and B columns a group touches are
-// reused from one L2. Bijective for any tile count and group size. The QKV projection
-// takes groups of four where that measured faster (at 4096 x 2304 each XCD then owns
-// four whole A row panels and every column tile; also at 16384 rows), but not for 4096
-// rows of 128 x 128 tiles over 27 column tiles (width 1152), where eight are faster. The
-// MLP up-projection, and the directly staged narrow GEMMs other than the MLP
-// down-projection, take four on grids of at least 64 tile rows; everything else eight.
+// reused from one L2. Bijective for any tile count and group size. Eight rows, but four
+// where that measured faster: the register-staged tiles of the QKV projection on grids of
+// at least 64 tile rows or at most 8 tile columns and of the MLP up-projection on at least
+// 64, and the 128 x 96 tiles of the narrow projections other than the MLP down-projection
+// on at least 64.
 constexpr int kXcds = 8;
 constexpr int kGroupM = 8;
 __device__ __forceinline__ void tile_coords(int nbm, int nbn, int& mt, int& nt, int GM = kGroupM) {
@@ -378,9 +400,9 @@ __device__ __forceinline__ void tile_coords(int nbm, int nbn, int& mt, int& nt, 
 // instead of in stalls between them. Loader chunks past the tile (when the chunk count
 // is not a multiple of the thread count) read zeros and land in a spare LDS slot, so
 // the block stays branch-free.
-template <int BM, int BN, int BK, int WM, int WN, int KSPLIT, EpiKind KIND>
-__global__ __launch_bounds__(WM * WN * KSPLIT * 64) void gemm_bf16_sched_kernel(GemmArgs a) {
-  constexpr int NT = WM * WN * KSPLIT * 64;
+template <int BM, int BN, int BK, int WM, int WN, EpiKind KIND>
+__global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_sched_kernel(GemmArgs a) {
+  constexpr int NT = WM * WN * 64;
   constexpr int LDK = BK + 8;  // LDS row pitch in bf16 (a 16-byte pad)
   constexpr int TM = BM / WM / 32;
   constexpr int TN = BN / WN / 32;
@@ -398,9 +420,7 @@ __global__ __launch_bounds__(WM * WN * KSPLIT * 64) void gemm_bf16_sched_kernel(
   constexpr int SMEM = AB_BYTES > C_BYTES ? AB_BYTES : C_BYTES;
   static_assert(SMEM <= LDS_CAP, "tile does not fit in LDS");
   static_assert(BM * (BN + kEpiPad) * 2 <= SMEM, "staged bf16 tile does not fit in LDS");
-  constexpr int KS = BK / 16 / KSPLIT;        // MFMA K steps per tile and wavefront
-  static_assert(KS * 16 * KSPLIT == BK, "K split must divide the K slice");
-  static_assert(KSPLIT == 1 || BM * CP * 4 <= AB_BYTES, "K-split partials must fit in LDS");
+  constexpr int KS = BK / 16;                 // MFMA K steps per tile
   constexpr int NMFMA = TM * TN * KS;
   constexpr int NDSR = (TM + TN) * KS;
   constexpr int NDSW = ACH + BCH;
@@ -412,10 +432,7 @@ __global__ __launch_bounds__(WM * WN * KSPLIT * 64) void gemm_bf16_sched_kernel(
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // wavefront (kg, wm, wn): sub-tile (wm, wn) over K quarter-slices kg*KS .. kg*KS+KS-1
-  // of every 64-wide K slice
-  const int kg = wave / (WM * WN), wmn = wave - kg * (WM * WN);
-  const int wm = wmn / WN, wn = wmn % WN;
+  const int wm = wave / WN, wn = wave % WN;
   const int l32 = lane & 31, g = lane >> 5;
   int mt, nt;
   {
@@ -506,8 +523,8 @@ __global__ __launch_bounds__(WM * WN * KSPLIT * 64) void gemm_bf16_sched_kernel(
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
   auto step = [&](auto fastc, int cur, int kt, bool write_next, bool load_next) {
-    const bf16* Ab = As + cur * BM * LDK + (wm * TM * 32 + l32) * LDK + g * 8 + kg * KS * 16;
-    const bf16* Bb = Bs + cur * BN * LDK + (wn * TN * 32 + l32) * LDK + g * 8 + kg * KS * 16;
+    const bf16* Ab = As + cur * BM * LDK + (wm * TM * 32 + l32) * LDK + g * 8;
+    const bf16* Bb = Bs + cur * BN * LDK + (wn * TN * 32 + l32) * LDK + g * 8;
     bf16x8 af[2][TM], bfr[2][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i) af[0][i] = *(const bf16x8*)(Ab + i * 32 * LDK);
@@ -573,38 +590,8 @@ __global__ __launch_bounds__(WM * WN * KSPLIT * 64) void gemm_bf16_sched_kernel(
   // The MFMAs compute C^T blocks (weights as the first operand), so in acc[i][j]
   // lane (l32, g) holds row (wm*TM + i)*32 + l32 of the tile and, in registers
   // 4q..4q+3, the four adjacent columns (wn*TN + j)*32 + 8q + 4g + 0..3.
-  if constexpr (KSPLIT == 2) {
-    // the second K half's partial sums go through LDS to the first half's wavefronts:
-    // one fixed order (first half + second half) for every element
-    float* P = (float*)smem;
-    if (kg == 1) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-            *(f32x4*)&P[((wm * TM + i) * 32 + l32) * CP + (wn * TN + j) * 32 + q * 8 + g * 4] = v;
-          }
-    }
-    __syncthreads();
-    if (kg == 0) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const f32x4 v = *(const f32x4*)&P[((wm * TM + i) * 32 + l32) * CP + (wn * TN + j) * 32 + q * 8 + g * 4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] += v[e];
-          }
-    }
-    __syncthreads();
-  }
   if constexpr (kBf16Out) {
-    bf16_epilogue<KIND, BM, BN, TM, TN, NT>(a, acc, (bf16*)smem, bias_s, m0, n0, wm, wn, l32, g, kg == 0, tid);
+    bf16_epilogue<KIND, BM, BN, TM, TN, NT>(a, acc, (bf16*)smem, bias_s, m0, n0, wm, wn, l32, g, true, tid);
   } else {
     float* Cs = (float*)smem;
 #pragma unroll
@@ -612,7 +599,7 @@ __global__ __launch_bounds__(WM * WN * KSPLIT * 64) void gemm_bf16_sched_kernel(
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
         const int rb0 = (wm * TM + i) * 32;
-        if (kg != 0 || rb0 < p * RP || rb0 >= (p + 1) * RP) continue;
+        if (rb0 < p * RP || rb0 >= (p + 1) * RP) continue;
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
@@ -924,6 +911,228 @@ __global__ __launch_bounds__(WM * WN * KSPLIT * 64) void gemm_bf16_dma_kernel(Ge
   }
 }
 
+// ---------------------------------------- bf16 / MFMA, direct staging, fragments ahead
+//
+// The directly staged tile computation with every wavefront owning a sub-tile over the
+// whole K slice (64x96, 64x64 or 32x96) and its fragments read one K step ahead, across
+// the slice boundary too. The last K step of a slice has its operands in registers when
+// the workgroup meets at the slice's one barrier, so that barrier frees the stage just
+// read: its refill (STAGES slices ahead) and the reads of the next slice's first
+// fragments go out under that step's MFMAs, and no MFMA waits for an LDS round trip.
+//
+// What bounds it: with the loads left out a 16384 x 1152 x 4608 launch of 128 x 192 tiles
+// takes 126 us (1380 TFLOP/s), with the MFMAs left out 170, with both 184; with every load
+// an L2 hit 153. So operand loads past L2 bind, and fewer operand bytes per output or more
+// workgroups per CU help while the order of the loop does not. A prefetch of the next
+// slices into L2 was worth 4 % on one shape and cost 5 % on others: not kept.
+//
+// HALVES: the two halves of every K slice accumulate apart and are added at the end, the
+// order of gemm_bf16_dma_kernel with a K split of two, so both give the same bits.
+template <int BM, int BN, int WM, int WN, int STAGES, int MINW, bool HALVES, EpiKind KIND>
+__global__ __launch_bounds__(WM * WN * 64, MINW) void gemm_bf16_pipe_kernel(GemmArgs a) {
+  constexpr int NT = WM * WN * 64, BK = 64, CPR = 8, KS = 4;
+  constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
+  static_assert(TM * WM * 32 == BM && TN * WN * 32 == BN, "wave grid must tile the block");
+  constexpr int ATOT = BM * CPR, BTOT = BN * CPR;
+  static_assert(ATOT % NT == 0 && BTOT % NT == 0, "whole rounds of chunks per slice");
+  constexpr int ACH = ATOT / NT, BCH = BTOT / NT, LPT = ACH + BCH;
+  static_assert(STAGES == 2 || STAGES == 3 || STAGES == 4, "two to four stages");
+  constexpr bool kBf16Out = KIND == EPI_GELU || KIND == EPI_QKV || KIND == EPI_KVX;
+  constexpr int SLICE = (ATOT + BTOT) * 16;
+  // after the main loop a stage buffer holds one half of the bf16 tile, or as many rows of
+  // the fp32 tile as fit
+  constexpr int HB = WM > 1 ? 2 : 1;  // bf16 halves
+  constexpr int EPIT = BM / HB * (BN + kEpiPad) * 2;
+  constexpr int EPIB = EPIT + BN * 4;  // and, in the first one, the tile's bias
+  constexpr int CP = BN + 4;
+  // fp32: one 32-row block of WPP wavefront rows per pass
+  constexpr int WFIT = SLICE / (32 * CP * 4);
+  constexpr int WPP = WFIT >= WM ? WM : WFIT >= 2 && WM % 2 == 0 ? 2 : 1;
+  constexpr int EPIF = WPP * 32 * CP * 4;
+  constexpr int EPI = kBf16Out ? EPIB : EPIF;
+  constexpr int SBA = SLICE > EPI ? SLICE : EPI;
+  static_assert(STAGES * SBA <= 160 * 1024, "stages do not fit in LDS");
+  __shared__ __attribute__((aligned(16))) char st0[SBA];
+  __shared__ __attribute__((aligned(16))) char st1[SBA];
+  __shared__ __attribute__((aligned(16))) char st2[STAGES > 2 ? SBA : 16];
+  __shared__ __attribute__((aligned(16))) char st3[STAGES > 3 ? SBA : 16];
+  auto stage = [&](auto s) -> char* {
+    constexpr int S = decltype(s)::value % STAGES;
+    if constexpr (S == 0) return st0;
+    else if constexpr (S == 1) return st1;
+    else if constexpr (S == 2) return st2;
+    else return st3;
+  };
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const int l32 = lane & 31, g = lane >> 5;
+  int mt, nt;
+  {
+    const int nbm = (a.M + BM - 1) / BM, nbn = (a.N + BN - 1) / BN;
+    tile_coords(nbm, nbn, mt, nt);
+  }
+  const int m0 = mt * BM, n0 = nt * BN;
+  if (!tile_live<KIND, BM>(a, m0)) return;  // uniform across the workgroup
+  // the tile's bias columns are fetched now and put into LDS after the main loop
+  static_assert(BN / 4 <= NT, "one bias load per thread");
+  f32x4 bias_v = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (kBf16Out) {
+    if (tid < BN / 4 && n0 + 4 * tid < a.N) bias_v = *(const f32x4*)(a.bias + n0 + 4 * tid);
+  }
+  int a_off[ACH], b_off[BCH], a_kc[ACH], b_kc[BCH];
+#pragma unroll
+  for (int i = 0; i < ACH; ++i) {
+    const int p = tid + i * NT, row = p / CPR;
+    a_kc[i] = ((p % CPR) ^ dma_swz<CPR>(row)) * 8;
+    a_off[i] = m0 + row < a.M ? ((m0 + row) * a.lda + a_kc[i]) * 2 : kOffOOB;
+  }
+#pragma unroll
+  for (int i = 0; i < BCH; ++i) {
+    const int p = tid + i * NT, row = p / CPR;
+    b_kc[i] = ((p % CPR) ^ dma_swz<CPR>(row)) * 8;
+    b_off[i] = n0 + row < a.N ? ((n0 + row) * a.ldb + b_kc[i]) * 2 : kOffOOB;
+  }
+  auto issue = [&](auto fast, char* sb, int kt) __attribute__((always_inline)) {
+    const int k0 = kt * BK;
+    const bool live = k0 < a.K;
+    const __amdgpu_buffer_rsrc_t ra =
+        buffer_rsrc((const char*)a.A + 2 * (size_t)k0, live ? (uint32_t)a.M * a.lda * 2 - 2 * k0 : 0u);
+    const __amdgpu_buffer_rsrc_t rb =
+        buffer_rsrc((const char*)a.B + 2 * (size_t)k0, live ? (uint32_t)a.N * a.ldb * 2 - 2 * k0 : 0u);
+    constexpr bool F = decltype(fast)::value;
+#pragma unroll
+    for (int i = 0; i < ACH; ++i)
+      buffer_load16_lds(ra, sb + (i * NT + wave * 64) * 16, F || k0 + a_kc[i] < a.K ? a_off[i] : kOffOOB);
+#pragma unroll
+    for (int i = 0; i < BCH; ++i)
+      buffer_load16_lds(rb, sb + (ATOT + i * NT + wave * 64) * 16, F || k0 + b_kc[i] < a.K ? b_off[i] : kOffOOB);
+  };
+
+  constexpr int NH = HALVES ? 2 : 1;
+  f32x16 accs[NH][TM][TN];
+#pragma unroll
+  for (int h = 0; h < NH; ++h)
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) accs[h][i][j][r] = 0.0f;
+  const int sw = dma_swz<CPR>(l32);
+  const int a_row = (wm * TM * 32 + l32) * CPR;
+  const int b_row = ATOT + (wn * TN * 32 + l32) * CPR;
+  bf16x8 af[2][TM], bfr[2][TN];
+  auto frags = [&](const char* cur, int buf, int kk) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) af[buf][i] = *(const bf16x8*)(cur + (a_row + i * 32 * CPR + ((g + 2 * kk) ^ sw)) * 16);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) bfr[buf][j] = *(const bf16x8*)(cur + (b_row + j * 32 * CPR + ((g + 2 * kk) ^ sw)) * 16);
+  };
+  auto mfmas = [&](int buf, int kk) __attribute__((always_inline)) {
+    const int h = HALVES ? kk / 2 : 0;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+        accs[h][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[buf][j], af[buf][i], accs[h][i][j], 0, 0, 0);
+  };
+  constexpr int NM = TM * TN, ND = TM + TN;
+  auto step = [&](auto fast, auto s, int kt) __attribute__((always_inline)) {
+    constexpr int S = decltype(s)::value;
+    const char* cur = stage(std::integral_constant<int, S>{});
+#pragma unroll
+    for (int kk = 0; kk + 1 < KS; ++kk) {
+      frags(cur, (kk + 1) & 1, kk + 1);
+      mfmas(kk & 1, kk);
+    }
+    // reads spread ahead of the MFMAs of their step
+#pragma unroll
+    for (int i = 0; i < (KS - 1) * ND; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, NM >= ND ? NM / ND : 1, 0);
+    }
+    // the last K step's operands are in registers: once every wavefront is here the stage
+    // can be refilled, and the next slice's first operands are read under this K step's MFMAs
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0<(STAGES - 2) * LPT>());
+    bare_barrier();
+    issue(fast, stage(std::integral_constant<int, S>{}), kt + STAGES);
+    frags(stage(std::integral_constant<int, S + 1>{}), 0, 0);
+    mfmas((KS - 1) & 1, KS - 1);
+#pragma unroll
+    for (int i = 0; i < NM; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x100, (ND + NM - 1) / NM, 0);
+      __builtin_amdgcn_sched_group_barrier(0x020, (LPT + NM - 1) / NM, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    }
+  };
+  const int nk = (a.K + BK - 1) / BK;
+  auto main_loop = [&](auto fast) __attribute__((always_inline)) {
+    issue(fast, stage(std::integral_constant<int, 0>{}), 0);
+    issue(fast, stage(std::integral_constant<int, 1>{}), 1);
+    if constexpr (STAGES > 2) issue(fast, stage(std::integral_constant<int, 2>{}), 2);
+    if constexpr (STAGES > 3) issue(fast, stage(std::integral_constant<int, 3>{}), 3);
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0<(STAGES - 1) * LPT>());
+    bare_barrier();
+    frags(stage(std::integral_constant<int, 0>{}), 0, 0);
+    int kt = 0;
+    for (; kt + STAGES <= nk; kt += STAGES) {
+      step(fast, std::integral_constant<int, 0>{}, kt);
+      step(fast, std::integral_constant<int, 1>{}, kt + 1);
+      if constexpr (STAGES > 2) step(fast, std::integral_constant<int, 2>{}, kt + 2);
+      if constexpr (STAGES > 3) step(fast, std::integral_constant<int, 3>{}, kt + 3);
+    }
+    if (kt < nk) step(fast, std::integral_constant<int, 0>{}, kt);
+    if constexpr (STAGES > 2)
+      if (kt + 1 < nk) step(fast, std::integral_constant<int, 1>{}, kt + 1);
+    if constexpr (STAGES > 3)
+      if (kt + 2 < nk) step(fast, std::integral_constant<int, 2>{}, kt + 2);
+  };
+  if (a.K % BK == 0)
+    main_loop(std::true_type{});
+  else
+    main_loop(std::false_type{});
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  f32x16(&acc)[TM][TN] = accs[0];
+  if constexpr (HALVES) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] += accs[1][i][j][r];
+  }
+  if constexpr (kBf16Out) {
+    float* bias_s = (float*)(st0 + EPIT);
+    if (tid < BN / 4) *(f32x4*)&bias_s[4 * tid] = bias_v;
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < HB; ++h)
+      bf16_epilogue<KIND, BM / HB, BN, TM, TN, NT>(a, acc, (bf16*)(h == 0 ? st0 : st1), bias_s, m0 + h * (BM / HB), n0,
+                                                   wm - h * (WM / HB), wn, l32, g, wm / (WM / HB) == h, tid);
+  } else {
+#pragma unroll
+    for (int p = 0; p < TM * (WM / WPP); ++p) {
+      const int i = p / (WM / WPP), w0 = p % (WM / WPP) * WPP;
+      float* Cs = (float*)(p % 2 == 0 ? st0 : st1);
+      if (wm >= w0 && wm < w0 + WPP) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+            *(f32x4*)&Cs[((wm - w0) * 32 + l32) * CP + (wn * TN + j) * 32 + q * 8 + g * 4] = v;
+          }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < WPP; ++w)
+        staged_epilogue<KIND, 32, BN, NT>(a, Cs + w * 32 * CP, CP, m0 + ((w0 + w) * TM + i) * 32, n0, tid);
+    }
+  }
+}
+
 // ------------------------------------------------------------------ fp32 / MFMA
 //
 // fp32 projections on v_mfma_f32_16x16x4_f32 (exact fp32 products and sums). Operand
@@ -1111,29 +1320,40 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_f32_kernel(GemmArgs a) {
   X(0, 64, 64, 2, 2)         \
   X(1, 32, 32, 2, 2)
 
-// Tile shapes (BM x BN x BK, wave grid WM x WN, K split). Per-wave tiles are 64x64,
-// 64x96 or 32x96; with a K split of 2 a second set of wavefronts takes the second half
-// of every K slice of the same tile. A CU spreads a workgroup's wavefronts round-robin
-// over its four SIMDs, so a wavefront count that is a multiple of four keeps them evenly
-// loaded (six wavefronts put two on two SIMDs and one on the others).
-#define SF_GEMM_TILES(X)          \
-  X(0, 128, 128, 64, 2, 2, 1)     \
-  X(1, 128, 288, 64, 4, 3, 1)     \
-  X(2, 128, 384, 64, 2, 4, 1)     \
-  X(3, 256, 192, 64, 4, 2, 1)     \
-  X(6, 128, 128, 128, 2, 2, 2)
+// bf16 tiles (BM x BN, wave grid WM x WN). A CU spreads a workgroup's wavefronts
+// round-robin over its four SIMDs, so a wavefront count that is a multiple of four keeps
+// them evenly loaded.
+//
+// Register-staged (64-wide K slices).
+#define SF_GEMM_TILES(X) X(kTile128, 128, 128, 64, 2, 2)
 
-// Directly staged tiles (as above, plus the number of LDS stages).
-#define SF_GEMM_DMA_TILES(X)           \
-  X(7, 128, 96, 64, 4, 1, 2, 4)
+// Directly staged, the K slice split over two sets of wavefronts (number of LDS stages).
+#define SF_GEMM_DMA_TILES(X)                \
+  X(kHalf128x96, 128, 96, 64, 4, 1, 2, 4)   \
+  X(kHalf128, 128, 128, 64, 2, 2, 2, 3)     \
+  X(kHalf64, 64, 64, 64, 2, 2, 2, 4)
+
+// Directly staged with the fragments read a K step ahead (LDS stages, wavefronts per
+// SIMD, both halves of a K slice summed apart).
+#define SF_GEMM_PIPE_TILES(X)                             \
+  X(kPipe256x192, 256, 192, 4, 2, 2, 2, false)            \
+  X(kPipe128x192, 128, 192, 2, 2, 2, 2, false)            \
+  X(kPipe128, 128, 128, 2, 2, 2, 2, false)                \
+  X(kPipe64, 64, 64, 2, 2, 4, 2, false)                   \
+  X(kPipeHalf128x192, 128, 192, 4, 2, 3, 2, true)         \
+  X(kPipeHalf128, 128, 128, 2, 2, 2, 2, true)
+
+enum GemmTile {
+  kTile128, kHalf128x96, kHalf128, kHalf64, kPipe256x192, kPipe128x192, kPipe128, kPipe64, kPipeHalf128x192, kPipeHalf128
+};
 
 template <EpiKind KIND>
 static hipError_t launch_bf16_tile(int tile, const GemmArgs& a, hipStream_t s) {
   switch (tile) {
-#define SF_TILE_CASE(id, bm, bn, bk, wm, wn, ks)                                                   \
+#define SF_TILE_CASE(id, bm, bn, bk, wm, wn)                                                       \
   case id:                                                                                         \
-    launch((gemm_bf16_sched_kernel<bm, bn, bk, wm, wn, ks, KIND>),                                 \
-           dim3(((a.N + bn - 1) / bn) * ((a.M + bm - 1) / bm)), dim3(wm * wn * ks * 64), 0, s, a); \
+    launch((gemm_bf16_sched_kernel<bm, bn, bk, wm, wn, KIND>),                                     \
+           dim3(((a.N + bn - 1) / bn) * ((a.M + bm - 1) / bm)), dim3(wm * wn * 64), 0, s, a);      \
     break;
     SF_GEMM_TILES(SF_TILE_CASE)
 #undef SF_TILE_CASE
@@ -1144,39 +1364,77 @@ static hipError_t launch_bf16_tile(int tile, const GemmArgs& a, hipStream_t s) {
     break;
     SF_GEMM_DMA_TILES(SF_DMA_TILE_CASE)
 #undef SF_DMA_TILE_CASE
+#define SF_PIPE_TILE_CASE(id, bm, bn, wm, wn, st, mw, hv)                                          \
+  case id:                                                                                         \
+    launch((gemm_bf16_pipe_kernel<bm, bn, wm, wn, st, mw, hv, KIND>),                              \
+           dim3(((a.N + bn - 1) / bn) * ((a.M + bm - 1) / bm)), dim3(wm * wn * 64), 0, s, a);      \
+    break;
+    SF_GEMM_PIPE_TILES(SF_PIPE_TILE_CASE)
+#undef SF_PIPE_TILE_CASE
     default:
       return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-// Tiles chosen from measurements on the 512^2 and 1024^2 projection shapes. Narrow
-// outputs (N <= 768, e.g. the attention output and MLP down-projections of the width-768
-// network) have too few wide tiles to fill the chip, so they take the directly staged
-// 128x96 tile (exactly one workgroup per CU at 4096x768) with each 64-wide K slice split
-// over two sets of wavefronts (4096x768x3072: 28.2 us, against 29.5 for the
-// register-staged 128x128 tile with 128-wide split slices, which remains for other
-// multiples of 128 up to 768). (At N = 1152 the 128x128 tiles outnumber the CUs, and a
-// split tile, one workgroup per CU, loses to the plain one, two per CU: 72 vs 67 us on
-// 4096x1152x4608.) The partial sums of the two halves are added in a fixed order, and
-// the choice depends on N and K only, never on M, so a row's result does not depend on
-// how many rows are in the batch. Otherwise 128x128 (64x64 per wavefront) is the
-// general tile; 128x384 (64x96 per wavefront, 8 wavefronts) and 128x288 (32x96 per
-// wavefront, 12 wavefronts: 4096x2304 in 22.5 instead of 23.6 us with 6 wavefronts of
-// 64x96) win when they cut the problem into exactly one workgroup per CU (e.g.
-// 4096x3072 and 4096x2304), and 256x192 (64x96 per wavefront, 8 wavefronts; 12 % fewer
-// operand bytes per CU than 128x384) beats 128x384 where it does so too (4096x3072:
-// 25.3 against 26.0 us per launch in the 512^2 step); these accumulate in the same
-// order, so switching among them with M changes no result bit.
-int choose_gemm_tile(int M, int N, int K) {
-  (void)K;
-  if (N % 96 == 0 && N <= 768) return 7;
-  if (N % 128 == 0 && N <= 768) return 6;
-  auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-  if (M % 256 == 0 && N % 192 == 0 && tiles(256, 192) == 256) return 3;
-  if (M % 128 == 0 && N % 384 == 0 && tiles(128, 384) == 256) return 2;
-  if (M % 128 == 0 && N % 288 == 0 && tiles(128, 288) == 256) return 1;
-  return 0;
+// Which tile. A row's result must not depend on how many rows are in the batch, so the
+// order in which K is summed follows from N alone: outputs up to 768 wide that are whole
+// multiples of 96 or 128 (the attention output and MLP down-projections of the narrower
+// networks) sum the two halves of every 64-wide slice apart and add them at the end,
+// everything else sums K in one go; within each of the two families every tile gives the
+// same bits, and M may choose. All times below are microseconds of one launch.
+//
+// Halves (4096 x 768: one 128 x 96 tile per CU; eight wavefronts hide the loads):
+//   * 64 x 64 while that is at most one and a half workgroups per CU: 1024 x 768 x 3072
+//     12.6 against 21.7 with 128 x 96, 2048 x 768 x 3072 22.8 against 23.1, but 2760 x 768 x
+//     3072 32.4 against 26.0 (up to two per CU where the alternative is 128 x 128:
+//     4096 x 512 x 2048 18.8 against 19.9);
+//   * 128 x 192, each wavefront holding both halves' sums, once it gives every CU a
+//     workgroup: it moves 28 % fewer operand bytes per output, and the loads are what binds
+//     these (8192 x 768 x 3072 49.8 against 56.0, 16384 x 768 x 3072 99 against 120);
+//   * 128 x 96, or for other multiples of 128 the 128 x 128 forms: both halves in each
+//     wavefront, two workgroups per CU, from one and a half per CU on (16384 x 512 x 2048
+//     44.6 against 48.1), else split over wavefronts (8192 x 512 x 2048 27.1 against 31.4).
+//
+// One go: 64 x 64 while that is at most one and a half workgroups per CU (1024 x 1152 x 4608
+// 28.5 against 37.8 with 128 x 128, 256 x 3072 x 768 5.5 against 9.3; 1024 x 2304 x 768, more
+// than two per CU, 13.1 against 11.1). Above, the tile with the least work on its busiest
+// CU: k = the most tiles a CU gets, times what a tile costs, relative to 128 x 128 tiles, as
+// fitted to launches of 1024 to 16384 rows (K 768 and 1152):
+//   * 128 x 128, register-staged: 11 for one, 8.9 k for more. Directly staged with the
+//     fragments ahead: 12 and 8.8 k (4096 x 1152 x 4608 61 against 72, 16384 x 3456 x 1152
+//     144 against 148; not for the GELU epilogue, 60 against 58 at 4096 x 4608 x 1152);
+//   * 128 x 192 with two workgroups per CU, one's main loop over the other's epilogue:
+//     18 and 12 k (4096 x 4608 x 1152 53 against 58, 16384 x 1152 x 4608 185 against 206);
+//   * 256 x 192, one workgroup per CU and the fewest operand bytes: 23.3 k (16384 x 2304 x
+//     768 68.6 against 73.6 with 128 x 192 and 78.9 with 128 x 128), 24.2 k where the GELU
+//     epilogue follows it more than once (16384 x 4608 x 1152 196 against 186).
+int choose_gemm_tile(int M, int N, EpiKind kind) {
+  auto tiles = [&](int bm, int bn) { return (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  constexpr long kCUs = 256;
+  const long small = tiles(64, 64);
+  if (N <= 768 && (N % 96 == 0 || N % 128 == 0)) {
+    if (2 * small <= 3 * kCUs) return kHalf64;
+    if (N % 192 == 0 && tiles(128, 192) >= kCUs) return kPipeHalf128x192;
+    if (N % 96 == 0) return kHalf128x96;
+    if (small <= 2 * kCUs) return kHalf64;
+    return 2 * tiles(128, 128) >= 3 * kCUs ? kPipeHalf128 : kHalf128;
+  }
+  if (2 * small <= 3 * kCUs) return kPipe64;
+  auto most = [&](int bm, int bn) { return (float)((tiles(bm, bn) + kCUs - 1) / kCUs); };
+  const float k128 = most(128, 128), k192 = most(128, 192), k256 = most(256, 192);
+  int best = kTile128;
+  float cost = k128 > 1 ? 8.9f * k128 : 11.0f;
+  auto take = [&](int tile, float c) {
+    if (c < cost) {
+      best = tile;
+      cost = c;
+    }
+  };
+  if (kind != EPI_GELU) take(kPipe128, k128 > 1 ? 8.8f * k128 : 12.0f);
+  take(kPipe128x192, k192 > 1 ? 12.0f * k192 : 18.0f);
+  take(kPipe256x192, (kind == EPI_GELU && k256 > 1 ? 24.2f : 23.3f) * k256);
+  return best;
 }
 
 int choose_gemm_f32_tile(int M, int N) {
@@ -1202,7 +1460,7 @@ static hipError_t launch_f32_tile(int tile, const GemmArgs& a, hipStream_t s) {
 
 template <EpiKind KIND>
 static hipError_t launch_kind(bool use_bf16, int tile, const GemmArgs& a, hipStream_t s) {
-  if (use_bf16) return launch_bf16_tile<KIND>(tile < 0 ? choose_gemm_tile(a.M, a.N, a.K) : tile, a, s);
+  if (use_bf16) return launch_bf16_tile<KIND>(tile < 0 ? choose_gemm_tile(a.M, a.N, KIND) : tile, a, s);
   return launch_f32_tile<KIND>(tile < 0 ? choose_gemm_f32_tile(a.M, a.N) : tile, a, s);
 }
 

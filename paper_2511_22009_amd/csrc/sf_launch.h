@@ -189,7 +189,7 @@ struct GemmArgs {
 hipError_t launch_gemm(bool use_bf16, EpiKind kind, const GemmArgs& a, hipStream_t s);
 // The same with an explicit bf16 tile shape (index into the tile table; -1 = choose).
 hipError_t launch_gemm_tile(bool use_bf16, int tile, EpiKind kind, const GemmArgs& a, hipStream_t s);
-int choose_gemm_tile(int M, int N, int K);
+int choose_gemm_tile(int M, int N, EpiKind kind);
 
 // ---- K4: softmax attention per (network row, head) ---------------------------------
 // Column of key t in the permuted transposed-v layout: bits 2 and 3 of t swapped, so in
