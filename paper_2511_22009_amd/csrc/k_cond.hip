@@ -21,7 +21,11 @@ constexpr int kGemvSamples = 4;  // samples per pass (inputs held in registers)
 // load sits behind a branch. Four samples' input slices stay in registers (read from
 // X, or built as the sinusoids of 1000 t). The RW x 4 row/sample partial sums leave
 // through butterfly reductions of 16 values. One task (RW rows) per wavefront.
-template <typename WT, int NC, int RW, int XMODE>
+// MANY: more than one pass of four samples. The weights are then loaded once, ahead of the
+// passes (56832 x 768 bf16 weights, 87 MB, 8 samples: 36.1 us with a load per pass, 31.2
+// so, 16 samples 63.5 and 47.8); a single pass keeps its own loads, whose registers it
+// shares with the inputs' (4 samples: 20.0 us, 23.0 with the form for many).
+template <typename WT, int NC, int RW, int XMODE, bool MANY>
 __device__ __forceinline__ void gemv_body(const GemvArgs& a, int bid) {
   constexpr int E = 16 / sizeof(WT);  // elements per 16-byte chunk
   static_assert(RW * kGemvSamples % 16 == 0, "rows x samples must fill butterfly groups");
@@ -34,7 +38,20 @@ __device__ __forceinline__ void gemv_body(const GemvArgs& a, int bid) {
   const int nchunk = a.K / E;
   const __amdgpu_buffer_rsrc_t w_src = buffer_rsrc(a.W, (uint32_t)((size_t)a.R * a.K * sizeof(WT)));
   const __amdgpu_buffer_rsrc_t x_src = buffer_rsrc(a.X, a.X ? (uint32_t)((size_t)a.B * a.ldx * 4) : 0u);
-  for (int b0 = 0; b0 < a.B; b0 += kGemvSamples) {
+  u32x4 w[RW][NC];
+  auto load_w = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int rr = 0; rr < RW; ++rr) {
+      const int j = min(j0 + rr, a.R - 1);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const int ch = lane + 64 * c;
+        w[rr][c] = buffer_load16_stream(w_src, ch < nchunk ? (int)(((uint32_t)j * a.K + ch * E) * sizeof(WT)) : kOffOOB);
+      }
+    }
+  };
+  if (MANY) load_w();
+  for (int b0 = 0; b0 < (MANY ? a.B : 1); b0 += kGemvSamples) {
     const int nb = min(kGemvSamples, a.B - b0);
     if constexpr (XMODE == 1) {
       // [cos | sin] of 1000 t times the frequency table, for this batch's samples
@@ -48,16 +65,7 @@ __device__ __forceinline__ void gemv_body(const GemvArgs& a, int bid) {
       }
       __syncthreads();
     }
-    u32x4 w[RW][NC];
-#pragma unroll
-    for (int rr = 0; rr < RW; ++rr) {
-      const int j = min(j0 + rr, a.R - 1);
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        const int ch = lane + 64 * c;
-        w[rr][c] = buffer_load16_stream(w_src, ch < nchunk ? (int)(((uint32_t)j * a.K + ch * E) * sizeof(WT)) : kOffOOB);
-      }
-    }
+    if (!MANY) load_w();
     float x[kGemvSamples][NC][E];
 #pragma unroll
     for (int bb = 0; bb < kGemvSamples; ++bb)
@@ -124,9 +132,9 @@ __device__ __forceinline__ void gemv_body(const GemvArgs& a, int bid) {
   }
 }
 
-template <typename WT, int NC, int RW, int XMODE>
+template <typename WT, int NC, int RW, int XMODE, bool MANY>
 __global__ __launch_bounds__(256) void gemv_kernel(GemvArgs a) {
-  gemv_body<WT, NC, RW, XMODE>(a, blockIdx.x);
+  gemv_body<WT, NC, RW, XMODE, MANY>(a, blockIdx.x);
 }
 
 // Rows per wavefront: keep the loads of a task within the register file. Eight rows up
@@ -141,16 +149,28 @@ template <typename WT, int NC>
 static void launch_gemv_nc(const GemvArgs& a, hipStream_t s) {
   constexpr int RW = gemv_rows_per_wave<WT, NC>();
   const int tasks = (a.R + RW - 1) / RW;
-  if (a.x_mode == 1)
-    launch((gemv_kernel<WT, NC, RW, 1>), dim3((tasks + 3) / 4), dim3(256), 0, s, a);
-  else
-    launch((gemv_kernel<WT, NC, RW, 0>), dim3((tasks + 3) / 4), dim3(256), 0, s, a);
+  const bool many = a.B > kGemvSamples;
+  const dim3 grid((tasks + 3) / 4);
+  if (a.x_mode == 1) {
+    // the sinusoids feed the fp32 timestep layer only
+    if constexpr (sizeof(WT) == 4) {
+      if (many)
+        launch((gemv_kernel<WT, NC, RW, 1, true>), grid, dim3(256), 0, s, a);
+      else
+        launch((gemv_kernel<WT, NC, RW, 1, false>), grid, dim3(256), 0, s, a);
+    }
+  } else if (many) {
+    launch((gemv_kernel<WT, NC, RW, 0, true>), grid, dim3(256), 0, s, a);
+  } else {
+    launch((gemv_kernel<WT, NC, RW, 0, false>), grid, dim3(256), 0, s, a);
+  }
 }
 
 template <typename WT>
 static hipError_t launch_gemv_t(const GemvArgs& a, hipStream_t s) {
   constexpr int E = 16 / sizeof(WT);
-  if (a.K % E || (size_t)a.R * a.K * sizeof(WT) >= (1ull << 31)) return hipErrorInvalidValue;
+  if (a.K % E || (size_t)a.R * a.K * sizeof(WT) >= (1ull << 31) || (a.x_mode == 1 && sizeof(WT) != 4))
+    return hipErrorInvalidValue;
   switch ((a.K / E + 63) / 64) {
     case 1: launch_gemv_nc<WT, 1>(a, s); break;
     case 2: launch_gemv_nc<WT, 2>(a, s); break;
@@ -301,10 +321,10 @@ hipError_t launch_embed(const EmbedArgs& a, hipStream_t s) {
 // their last round (1776 of them at 512^2, three per CU: 2.3 rounds). So the embed's
 // workgroups follow the GEMV's in the same launch, filling that round, instead of
 // running as a launch of their own. Each part computes exactly what its own kernel does.
-template <typename WT, int NC, int RW>
+template <typename WT, int NC, int RW, bool MANY>
 __global__ __launch_bounds__(256) void gemv_embed_kernel(GemvArgs g, EmbedArgs e, int n_gemv) {
   if ((int)blockIdx.x < n_gemv)
-    gemv_body<WT, NC, RW, 0>(g, blockIdx.x);
+    gemv_body<WT, NC, RW, 0, MANY>(g, blockIdx.x);
   else
     embed_p2c4_body(e, blockIdx.x - n_gemv);
 }
@@ -321,7 +341,10 @@ static void launch_gemv_embed_nc(const GemvArgs& g, const EmbedArgs& e, hipStrea
   constexpr int RW = gemv_rows_per_wave<WT, NC>();
   const int n_gemv = ((g.R + RW - 1) / RW + 3) / 4;
   const int n_embed = (e.rows * e.N + kEmbedWgTok - 1) / kEmbedWgTok;
-  launch((gemv_embed_kernel<WT, NC, RW>), dim3(n_gemv + n_embed), dim3(256), 0, s, g, e, n_gemv);
+  if (g.B > kGemvSamples)
+    launch((gemv_embed_kernel<WT, NC, RW, true>), dim3(n_gemv + n_embed), dim3(256), 0, s, g, e, n_gemv);
+  else
+    launch((gemv_embed_kernel<WT, NC, RW, false>), dim3(n_gemv + n_embed), dim3(256), 0, s, g, e, n_gemv);
 }
 
 hipError_t launch_gemv_embed(bool w_bf16, const GemvArgs& g, const EmbedArgs& e, hipStream_t s) {
