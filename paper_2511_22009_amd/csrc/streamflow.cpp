@@ -656,9 +656,11 @@ void drop_graphs(sf_model* m) {
 // Runs `enqueue` (which launches the call's kernels on s) through the graph cache: a
 // cached graph for `key` is replayed; otherwise the launches are captured, instantiated,
 // cached and replayed. Eager when graphs are off, on the null stream, or while timing.
-template <typename F>
-int run_graphed(sf_model* m, const std::vector<char>& key, hipStream_t s, F&& enqueue) {
+// `make_key` gives the call's key, asked for only then.
+template <typename K, typename F>
+int run_graphed(sf_model* m, K&& make_key, hipStream_t s, F&& enqueue) {
   if (!m->graph_on || s == nullptr || any_timing(m)) return enqueue();
+  const std::vector<char> key = make_key();
   for (auto& g : m->graphs) {
     if (g.key == key) {
       g.used = ++m->graph_clock;
@@ -837,7 +839,7 @@ int sf_velocity(sf_model* m, const float* x, const float* t, int B, const sf_con
   hipStream_t s = (hipStream_t)stream;
   const bool ready = modulation_cached(m, t, B, s);
   if (ready) ++m->mod_skips;
-  const int rc = run_graphed(m, call_key(m, 0, x, v, nullptr, nullptr, B, t, nullptr, cond, s, ready), s, [&]() -> int {
+  const int rc = run_graphed(m, [&] { return call_key(m, 0, x, v, nullptr, nullptr, B, t, nullptr, cond, s, ready); }, s, [&]() -> int {
     SF_TRY(run_network(m, x, t, B, rows, cond, m->hd.L, guided ? m->vrows : v, s, ready));
     if (guided) return timed(m, SF_KC_EULER, s, [&]() { return sf::launch_cfg_combine(m->vrows, B, m->E, w, v, s); });
     return SF_OK;
@@ -857,7 +859,7 @@ int sf_stream_step(sf_model* m, float* x, const float* t, const float* dt, int B
   hipStream_t s = (hipStream_t)stream;
   const bool ready = modulation_cached(m, t, B, s);
   if (ready) ++m->mod_skips;
-  const int rc = run_graphed(m, call_key(m, 1, x, z_new, x_done, nullptr, B, t, dt, cond, s, ready), s, [&]() -> int {
+  const int rc = run_graphed(m, [&] { return call_key(m, 1, x, z_new, x_done, nullptr, B, t, dt, cond, s, ready); }, s, [&]() -> int {
     SF_TRY(run_network(m, x, t, B, rows, cond, m->hd.L, m->vrows, s, ready));
     return timed(m, SF_KC_EULER, s, [&]() {
       sf::EulerArgs a{};
