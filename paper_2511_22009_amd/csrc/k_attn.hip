@@ -864,12 +864,9 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_dma72x2_kernel(AttnArgs a) {
   // below 1152, else nothing (the load reads zeros into the spare slot). Whole
   // wavefronts fall in one part, since both parts are multiples of 64 chunks.
   int goff[LPT];
-  bool isk[LPT], inr[LPT];
 #pragma unroll
   for (int i = 0; i < LPT; ++i) {
     const int p = i * 256 + tid;
-    isk[i] = p < kD72K;
-    inr[i] = p < NCH;
     if (p < kD72K) {
       goff[i] = p * 16;
     } else if (p < NCH) {
@@ -879,6 +876,9 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_dma72x2_kernel(AttnArgs a) {
       goff[i] = kOffOOB;
     }
   }
+  // the part a wavefront's chunks fall in follows from its (scalar) index: chosen from the
+  // thread index instead, the resource of a load is a vector value, which the compiler
+  // makes uniform again in a loop of its own around every load
   auto issue = [&](char* sb, int step) {
     const int kv0 = step * 2 * kKH;
     const __amdgpu_buffer_rsrc_t k_src =
@@ -886,10 +886,10 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_dma72x2_kernel(AttnArgs a) {
     const __amdgpu_buffer_rsrc_t v_src = buffer_rsrc(Vt + kv0, (uint32_t)max(DH * a.ldv - kv0, 0) * 2);
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
-      // the wavefront's part is uniform (the parts are whole wavefronts)
-      char* dst = inr[i] ? sb + (isk[i] ? (i * 256 + wave * 64) * 16 : V_OFF + (i * 256 + wave * 64 - kD72K) * 16)
-                         : g_attn72_spare;
-      buffer_load16_lds(isk[i] ? k_src : v_src, dst, goff[i]);
+      const int p0 = i * 256 + wave * 64;
+      const bool isk = p0 < kD72K;
+      char* dst = p0 < NCH ? sb + (isk ? p0 * 16 : V_OFF + (p0 - kD72K) * 16) : g_attn72_spare;
+      buffer_load16_lds(isk ? k_src : v_src, dst, goff[i]);
     }
   };
 
