@@ -94,3 +94,28 @@ def test_gemm_fp32_tiles_and_ragged_k():
         assert rel_l2(got[k], oracle.forward_one(om, x[k], t[k], dtype=np.float64)) < 2e-6
         np.testing.assert_array_equal(host(m.velocity(put(x[k:k + 1]), t[k:k + 1]))[0], got[k])
     m.close()
+
+
+@pytest.mark.parametrize("C,p,H,Wd,D,heads", [(4, 2, 14, 22, 192, 4), (8, 2, 6, 10, 128, 4), (3, 2, 10, 6, 72, 1),
+                                              (1, 4, 20, 12, 200, 5), (4, 1, 3, 5, 1160, 29), (2, 4, 16, 8, 8, 1),
+                                              (4, 2, 2, 2, 2048, 16)])
+def test_head_fp32(C, p, H, Wd, D, heads):
+    """Final LayerNorm, modulate and output map alone (a network without blocks): patches of
+    4 to 32 values, widths that fill no column step, token counts that end inside a
+    workgroup's 16 rows (and put each slot's rows elsewhere in it): against the oracle in 64
+    bits, and every slot alone gives its bits in the batch."""
+    import oracle
+    cfg = W.Config("head", C=C, H=H, W=Wd, p=p, D=D, L=0, heads=heads, mlp=D, K=5, schedule="uniform5")
+    tens = W.make_weights(cfg, init="tsens")
+    tens["pos"] = np.random.default_rng(4).standard_normal((cfg.N, D)).astype(np.float32)
+    blob = W.write_blob(cfg, tens)
+    m = Model(blob, Precision.FP32, 5)
+    x = W.latents(cfg, 5, seed=9)
+    t = np.random.default_rng(10).uniform(0.0, 1.0, 5).astype(np.float32)
+    put = lambda a: torch.from_numpy(a).cuda()  # noqa: E731
+    got = host(m.velocity(put(x), t))
+    om = oracle.load_blob(blob)
+    for k in range(5):
+        assert rel_l2(got[k], oracle.forward_one(om, x[k], t[k], dtype=np.float64)) < 2e-6
+        np.testing.assert_array_equal(host(m.velocity(put(x[k:k + 1]), t[k:k + 1]))[0], got[k])
+    m.close()
