@@ -25,6 +25,8 @@ CASES = {
     # output and down-projection 384: 128 x 192 with both halves in a wavefront (K 384, 776),
     # QKV 1152: 128 x 192; 748 tokens: v leaves in groups of four tokens
     "w384": (384, 6, 776, 44, 68, 64),
+    # QKV 2280: 128 x 288 (4095 rows, 195 tokens, K 760)
+    "w760": (760, 19, 520, 26, 30, 21),
     # output and down-projection 640: 128 x 128 with the halves over two wavefronts
     "w640": (640, 10, 640, 16, 24, 64),
 }
