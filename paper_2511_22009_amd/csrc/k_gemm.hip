@@ -1140,8 +1140,11 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void gemm_bf16_pipe_kernel(Gemm
 // ahead, in the layout of the bf16 kernel above (rows of eight 16-byte chunks, swizzled).
 // An MFMA contracts four values, one per lane group g = lane / 16; a lane reads whole
 // chunks (chunk 4 kk + g of its row) and feeds MFMA (kk, e) their element e, so that MFMA
-// sums columns 16 kk + 4 g + e of the slice. Every tile shape sums K in this one order, so
-// the choice of a tile, by M too, changes no result bit.
+// sums columns 16 kk + 4 g + e of the slice. The four elements e have sums of their own, added
+// at the end: a quarter of the chain's length and so less rounding (velocity of two 512^2
+// blocks 2.4e-7 off 64 bits, 3.1e-7 to 3.7e-7 in one chain, for 1.5 % of the call's time).
+// Every tile shape sums K in this one order, so the choice of a tile, by M too, changes no
+// result bit.
 //
 // The weights are the first operand: lane (l16, g) ends up with four adjacent output
 // columns 4 g .. 4 g + 3 of row l16 of each 16 x 16 block, which leave as 16-byte accesses
@@ -1252,11 +1255,13 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_f32_kernel(GemmArgs a) {
       buffer_load16_lds(rb, sb + (ATOT + i * NT + wave * 64) * 16, k0 + b_kc[i] < a.K ? b_off[i] : kOffOOB);
   };
 
-  f32x4 acc[TM][TN];
+  f32x4 accs[4][TM][TN];  // one sum per element of a chunk
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+  for (int e = 0; e < 4; ++e)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) accs[e][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int sw = dma_swz<CPR>(l16);  // row blocks are 16 apart: every row of a lane shares it
   const int a_row = (wm * TM * 16 + l16) * CPR, b_row = ATOT + (wn * TN * 16 + l16) * CPR;
 
@@ -1283,7 +1288,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_f32_kernel(GemmArgs a) {
         for (int i = 0; i < TM; ++i)
 #pragma unroll
           for (int j = 0; j < TN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bf[kk][j][e], af[kk][i][e], acc[i][j], 0, 0, 0);
+            accs[e][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bf[kk][j][e], af[kk][i][e], accs[e][i][j], 0, 0, 0);
   };
 
   const int nk = (a.K + BK - 1) / BK;
@@ -1306,7 +1311,11 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_f32_kernel(GemmArgs a) {
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       const int n = n0 + (wn * TN + j) * 16 + g * 4;
-      if (n < a.N) f32_epilogue4<KIND>(a, m, n, acc[i][j]);
+      f32x4 acc;
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        acc[c] = (accs[0][i][j][c] + accs[1][i][j][c]) + (accs[2][i][j][c] + accs[3][i][j][c]);
+      if (n < a.N) f32_epilogue4<KIND>(a, m, n, acc);
     }
   }
 }
