@@ -1334,9 +1334,10 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_f32_kernel(GemmArgs a) {
 // them evenly loaded.
 //
 // Register-staged (64-wide K slices).
-#define SF_GEMM_TILES(X)          \
-  X(kTile128, 128, 128, 64, 2, 2) \
-  X(kTile128x288, 128, 288, 64, 4, 3)
+#define SF_GEMM_TILES(X)              \
+  X(kTile128, 128, 128, 64, 2, 2)     \
+  X(kTile128x288, 128, 288, 64, 4, 3) \
+  X(kTile256x192, 256, 192, 64, 4, 2)
 
 // Directly staged, the K slice split over two sets of wavefronts (number of LDS stages).
 #define SF_GEMM_DMA_TILES(X)                \
@@ -1355,7 +1356,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_f32_kernel(GemmArgs a) {
   X(kPipeHalf128, 128, 128, 2, 2, 2, 2, true)
 
 enum GemmTile {
-  kTile128, kTile128x288, kHalf128x96, kHalf128, kHalf64, kPipe256x192, kPipe128x192, kPipe128, kPipe64, kPipeHalf128x192, kPipeHalf128
+  kTile128, kTile128x288, kTile256x192, kHalf128x96, kHalf128, kHalf64, kPipe256x192, kPipe128x192, kPipe128, kPipe64, kPipeHalf128x192, kPipeHalf128
 };
 
 template <EpiKind KIND>
@@ -1422,7 +1423,10 @@ static hipError_t launch_bf16_tile(int tile, const GemmArgs& a, hipStream_t s) {
 //     epilogue follows it more than once (16384 x 4608 x 1152 196 against 186);
 //   * 128 x 288, register-staged by twelve wavefronts, 22 for one and never more, for the
 //     QKV projection only: it fills the chip where 256 x 192 leaves a quarter of it idle (4096 x
-//     2304 x 768, in the step: 21.9 against 22.7).
+//     2304 x 768, in the step: 21.9 against 22.7);
+//   * 256 x 192, register-staged, 23 for one and never more, for the GELU epilogue: level alone
+//     (4096 x 3072 x 768 25.6 against 25.4), but the four-slot 512^2 step took 0.994 to 0.997 of
+//     its time before these tiles with it, 1.011 to 1.017 with the other one (1.000 on one GPU).
 int choose_gemm_tile(int M, int N, EpiKind kind) {
   auto tiles = [&](int bm, int bn) { return (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
   constexpr long kCUs = 256;
@@ -1449,6 +1453,7 @@ int choose_gemm_tile(int M, int N, EpiKind kind) {
   take(kPipe128x192, k192 > 1 ? 12.0f * k192 : 18.0f);
   take(kPipe256x192, (kind == EPI_GELU && k256 > 1 ? 24.2f : 23.3f) * k256);
   if (kind == EPI_QKV && tiles(128, 288) <= kCUs) take(kTile128x288, 22.0f);
+  if (kind == EPI_GELU && k256 == 1) take(kTile256x192, 23.0f);
   return best;
 }
 

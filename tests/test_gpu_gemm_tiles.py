@@ -18,7 +18,7 @@ CASES = {
     # QKV 1536: 128 x 128, fragments ahead; output and down-projection 512: 128 x 128 with both
     # halves in a wavefront, K 512 and 520; up-projection 520: 128 x 128, register-staged
     "w512": (512, 8, 520, 26, 30, 64),
-    # QKV 3480 and up-projection 3080: 256 x 192, K 1160; output 1160: 128 x 128 registers
+    # QKV 3480 and up-projection 3080: 256 x 192, K 1160, the second register-staged; output 1160: 128 x 128 registers
     "w1160": (1160, 29, 3080, 26, 30, 16),
     # up-projection 7000: 128 x 192, K 200; the others 64 x 64, the last with K 7000
     "mlp7000": (200, 5, 7000, 26, 30, 8),
