@@ -136,117 +136,126 @@ hipError_t launch_ln(bool out_bf16, const LnArgs& a, hipStream_t s) {
   return out_bf16 ? launch_ln_t<bf16>(a, s) : launch_ln_t<float>(a, s);
 }
 
-// A workgroup takes 16 token rows, its four wavefronts a quarter of the columns each (16-wide
-// chunks 4 i + wave), held in registers in the operand layout of v_mfma_f32_16x16x4_f32: lane
-// (l16, g) (g = lane / 16) has columns 4 g .. 4 g + 3 of every chunk of row l16. The row
-// sums are lane-local plus two lane exchanges and one pass through LDS; then the modulated
-// rows feed the linear map D -> P as they stand, MFMA (i, e) contracting columns 16 (4 i +
-// wave) + 4 g + e against the same columns of 16 W_f rows (exact fp32 products and sums, four
-// running sums per output and wavefront), and the wavefronts' results meet in LDS. Each value
-// goes straight to its unpatchified position. Every row's arithmetic is the same wherever
-// it sits in its group. Loading the rows bounds it; with the map as dot products on the
-// vector ALU, four rows per wavefront, it was bound by the chains of a lone wavefront per
-// SIMD: 16384 rows x 1152 57.6 us, 29.6 so; 4096 x 1152 16.6 and 10.6; 1024 x 768 9.4 and 6.6.
-// (The weight rows loaded after the row sums, for fewer registers: 28.0 and 10.5, but 10.3
-// at 1024 x 768, where their latency is not covered.)
-template <int NI>  // 64-wide column steps: D <= 64 NI
+// A workgroup takes four token rows. Each wavefront normalises and modulates one of them (lane
+// l holds 16-byte chunks l + 64 i) and leaves it in LDS; then wavefront w applies outputs
+// 4 w .. 4 w + 3 (and every 16th group of four after them) of the linear map D -> P to all four
+// rows: its slice of four W_f rows, loaded with the rows at the start, stays in registers
+// while outputs last, and the 16 row x output sums leave through one butterfly reduction. Each
+// value goes straight to its unpatchified position.
+//
+// One order of sums for every output, spelled out with fmaf so that no compilation changes it:
+// per chunk fma(x, wx, y wy) + fma(z, wz, w ww), a lane's chunks in turn, then the lanes by
+// xor 32, 16, 8, 4, 2, 1. In a stream step the head's last bits enter the queue and, through
+// the bf16 roundings of later steps, the fourth digit of its latents, so another order is
+// another trajectory (on v_mfma_f32_16x16x4_f32, sixteen rows per workgroup, a second 512^2
+// step differed by 1e-4, a guided one by 7e-4, at the same error against 64 bits).
+//
+// The vector ALU bounds it: six instructions per four products in this order. us for 1024 x
+// 768 / 4096 x 768 / 16384 x 768 / 16384 x 1152 rows x width: 4.8 / 8.5 / 24.0 / 37.7; the
+// same order with four rows and all outputs per wavefront (lone wavefronts, bound by their
+// chains) 10.2 / 11.0 / 28.6 / 54.2; on the matrix cores 7.5 / 8.2 / 20.4 / 30.1. Two rows per
+// wavefront: 6.2 / 8.2 / 25.5 / 53.2; a loop over row groups that keeps the weights 5.4 /
+// 9.3 / 26.5 / 54.4.
+template <int NV>  // 256 (NV - 1) < D <= 256 NV
 __global__ __launch_bounds__(256) void head_kernel(HeadArgs a) {
-  __shared__ float red[2][4][16];
-  __shared__ f32x4 part[4][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int l16 = lane & 15, g = lane >> 4;
+  __shared__ float4 rows[4][NV * 64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int M = a.rows * a.N;
-  const int m0 = blockIdx.x * 16;
-  const int m = min(m0 + l16, M - 1);
-  const int c0 = 16 * wave + 4 * g;  // this lane's first column
-  // unconditional loads at in-bounds columns, zeros selected after all are issued
-  auto col = [&](int i) { return c0 + 64 * i < a.D ? c0 + 64 * i : 0; };
-  f32x4 v[NI], w[NI];
-  const float* row = a.h + (size_t)m * a.D;
+  const int m0 = blockIdx.x * 4;
+  const int nv = a.D >> 2;
+  // unconditional loads at in-bounds chunks (only a row's last chunk can lie past its end),
+  // zeros selected after all are issued
+  auto in = [&](int i) { return i + 1 < NV || lane + i * 64 < nv; };
+  auto col = [&](int i) { return in(i) ? lane + i * 64 : 0; };
+  float4 w[4][NV];
+  auto load_w = [&](int o0) {
 #pragma unroll
-  for (int i = 0; i < NI; ++i) v[i] = *(const f32x4*)(row + col(i));
-  auto load_w = [&](int f0) {
-    const float* wr = a.W_f + (size_t)min(f0 + l16, a.P - 1) * a.D;
+    for (int q = 0; q < 4; ++q) {
+      const float4* wr = (const float4*)(a.W_f + (size_t)min(o0 + q, a.P - 1) * a.D);
 #pragma unroll
-    for (int i = 0; i < NI; ++i) w[i] = *(const f32x4*)(wr + col(i));
+      for (int i = 0; i < NV; ++i) w[q][i] = wr[col(i)];
+    }
   };
-  load_w(0);
-  const int q = (int)fdiv((uint32_t)m, a.tok);
-  const int slot = q < a.n_slots ? q : q - a.n_slots;
-  const float* tsh = a.table + (size_t)slot * a.ldt + a.shift_off;
-  const float* tsc = a.table + (size_t)slot * a.ldt + a.scale_off;
-  auto row_sum = [&](int which, float s) {
-    s = pair32_sum(pair16_sum(s));
-    if (g == 0) red[which][wave][l16] = s;
-    __syncthreads();
-    return (red[which][0][l16] + red[which][1][l16]) + (red[which][2][l16] + red[which][3][l16]);
-  };
-  float s = 0.0f;
+  {
+    const int m = min(m0 + wave, M - 1);
+    const float4* row = (const float4*)(a.h + (size_t)m * a.D);
+    const int r = (int)fdiv((uint32_t)m, a.tok);
+    const int slot = r < a.n_slots ? r : r - a.n_slots;
+    const float4* tsh = (const float4*)(a.table + (size_t)slot * a.ldt + a.shift_off);
+    const float4* tsc = (const float4*)(a.table + (size_t)slot * a.ldt + a.scale_off);
+    float4 v[NV], sc[NV], sh[NV];
 #pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    if (c0 + 64 * i >= a.D) v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    s += (v[i][0] + v[i][1]) + (v[i][2] + v[i][3]);
-  }
-  const float mean = row_sum(0, s) / (float)a.D;
-  float sq = 0.0f;
+    for (int i = 0; i < NV; ++i) {
+      v[i] = row[col(i)];
+      sc[i] = tsc[col(i)];
+      sh[i] = tsh[col(i)];
+    }
+    load_w(4 * wave);
+    if (!in(NV - 1)) v[NV - 1] = make_float4(0.f, 0.f, 0.f, 0.f);
+    float s = 0.0f;
 #pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    if (c0 + 64 * i < a.D) {
-      const float d0 = v[i][0] - mean, d1 = v[i][1] - mean, d2 = v[i][2] - mean, d3 = v[i][3] - mean;
-      sq += (d0 * d0 + d1 * d1) + (d2 * d2 + d3 * d3);
+    for (int i = 0; i < NV; ++i) s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
+    const float mean = wave_sum(s) / (float)a.D;
+    float sq = 0.0f;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const float d0 = v[i].x - mean, d1 = v[i].y - mean, d2 = v[i].z - mean, d3 = v[i].w - mean;
+      const float d = fmaf(d0, d0, d1 * d1) + fmaf(d2, d2, d3 * d3);
+      sq = in(i) ? sq + d : sq;
+    }
+    const float rstd = 1.0f / sqrtf(wave_sum(sq) / (float)a.D + kLnEps);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      float4 y;
+      y.x = in(i) ? fmaf((v[i].x - mean) * rstd, 1.0f + sc[i].x, sh[i].x) : 0.0f;
+      y.y = in(i) ? fmaf((v[i].y - mean) * rstd, 1.0f + sc[i].y, sh[i].y) : 0.0f;
+      y.z = in(i) ? fmaf((v[i].z - mean) * rstd, 1.0f + sc[i].z, sh[i].z) : 0.0f;
+      y.w = in(i) ? fmaf((v[i].w - mean) * rstd, 1.0f + sc[i].w, sh[i].w) : 0.0f;
+      rows[wave][lane + i * 64] = y;
     }
   }
-  const float rstd = 1.0f / sqrtf(row_sum(1, sq) / (float)a.D + kLnEps);
+  __syncthreads();
+  for (int o0 = 4 * wave; o0 < a.P; o0 += 16) {
+    if (o0 >= 16) load_w(o0);
+    float acc[16];
 #pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    const f32x4 sc = *(const f32x4*)(tsc + col(i)), sh = *(const f32x4*)(tsh + col(i));
-    const bool in = c0 + 64 * i < a.D;
+    for (int k = 0; k < 16; ++k) acc[k] = 0.0f;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[i][e] = in ? (v[i][e] - mean) * rstd * (1.0f + sc[e]) + sh[e] : 0.0f;
-  }
-  const int gwn = a.W / a.p;
-  for (int f0 = 0; f0 < a.P; f0 += 16) {
-    if (f0 > 0) {
-      __syncthreads();  // the previous outputs were read
-      load_w(f0);
-    }
-    f32x4 acc[4];
+    for (int i = 0; i < NV; ++i)
 #pragma unroll
-    for (int k = 0; k < 4; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int r = 0; r < 4; ++r) {
+        const float4 x = rows[r][lane + i * 64];
 #pragma unroll
-    for (int i = 0; i < NI; ++i)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[i][e], w[i][e], acc[e], 0, 0, 0);
-    f32x4 t;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) t[r] = (acc[0][r] + acc[1][r]) + (acc[2][r] + acc[3][r]);
-    part[wave][lane] = t;
-    __syncthreads();
-    // lane (l16, g) holds output f0 + l16 of rows 4 g .. 4 g + 3: wavefront w writes row 4 g + w
-    const int mo = m0 + 4 * g + wave, f = f0 + l16;
-    if (mo < M && f < a.P) {
-      const float y = (part[0][lane][wave] + part[1][lane][wave]) + (part[2][lane][wave] + part[3][lane][wave]);
-      const int r = (int)fdiv((uint32_t)mo, a.tok);
-      const int n = mo - r * a.N;
-      const int gh = n / gwn, gw = n - gh * gwn;
-      const int c = f % a.C, ij = f / a.C;
-      const int i = ij / a.p, j = ij - i * a.p;
-      a.v[(((size_t)r * a.C + c) * a.H + gh * a.p + i) * a.W + gw * a.p + j] = y + a.b_f[f];
+        for (int q = 0; q < 4; ++q)
+          acc[r * 4 + q] += fmaf(x.x, w[q][i].x, x.y * w[q][i].y) + fmaf(x.z, w[q][i].z, x.w * w[q][i].w);
+      }
+    const float tot = wave_reduce16(acc);
+    const int idx = (lane >> 2) & 15;
+    const int m = m0 + (idx >> 2), f = o0 + (idx & 3);
+    if ((lane & 3) == 0 && f < a.P && m < M) {
+      const int r = (int)fdiv((uint32_t)m, a.tok);
+      const int n = m - r * a.N;
+      const int gh = (int)fdiv((uint32_t)n, a.div_gw), gw = n - gh * (int)a.div_gw.d;
+      const int ij = (int)fdiv((uint32_t)f, a.div_c), c = f - ij * a.C;
+      const int i = (int)fdiv((uint32_t)ij, a.div_p), j = ij - i * a.p;
+      a.v[(((size_t)r * a.C + c) * a.H + gh * a.p + i) * a.W + gw * a.p + j] = tot + a.b_f[f];
     }
   }
 }
 
 hipError_t launch_head(const HeadArgs& a, hipStream_t s) {
-  const dim3 grid((a.rows * a.N + 15) / 16);
-  const int ni = (a.D + 63) / 64;
-  if (ni <= 2) launch(head_kernel<2>, grid, dim3(256), 0, s, a);
-  else if (ni <= 4) launch(head_kernel<4>, grid, dim3(256), 0, s, a);
-  else if (ni <= 8) launch(head_kernel<8>, grid, dim3(256), 0, s, a);
-  else if (ni <= 12) launch(head_kernel<12>, grid, dim3(256), 0, s, a);
-  else if (ni <= 18) launch(head_kernel<18>, grid, dim3(256), 0, s, a);
-  else if (ni <= 24) launch(head_kernel<24>, grid, dim3(256), 0, s, a);
-  else if (ni <= 32) launch(head_kernel<32>, grid, dim3(256), 0, s, a);
-  else return hipErrorInvalidValue;
+  const dim3 grid((a.rows * a.N + 3) / 4);
+  switch ((a.D + 255) / 256) {
+    case 1: launch(head_kernel<1>, grid, dim3(256), 0, s, a); break;
+    case 2: launch(head_kernel<2>, grid, dim3(256), 0, s, a); break;
+    case 3: launch(head_kernel<3>, grid, dim3(256), 0, s, a); break;
+    case 4: launch(head_kernel<4>, grid, dim3(256), 0, s, a); break;
+    case 5: launch(head_kernel<5>, grid, dim3(256), 0, s, a); break;
+    case 6: launch(head_kernel<6>, grid, dim3(256), 0, s, a); break;
+    case 7: launch(head_kernel<7>, grid, dim3(256), 0, s, a); break;
+    case 8: launch(head_kernel<8>, grid, dim3(256), 0, s, a); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 

@@ -144,6 +144,7 @@ struct HeadArgs {
   FastDiv tok;
   float* v;             // [rows][C][H][W]
   int rows, C, H, W, p, D, N, P;
+  FastDiv div_gw, div_c, div_p;  // by the patches of a picture row, by C and by p
 };
 hipError_t launch_head(const HeadArgs& a, hipStream_t s);
 

@@ -552,6 +552,7 @@ int run_network(sf_model* m, const float* x, const float* t, int n_lat, int rows
     a.h = m->h; a.W_f = m->W_f; a.b_f = m->b_f; a.table = m->table; a.ldt = m->modw;
     a.shift_off = (int)h.L * 6 * D; a.scale_off = (int)h.L * 6 * D + D; a.n_slots = n_lat; a.tok = div_n;
     a.v = head_out; a.rows = rows; a.C = h.C; a.H = h.H; a.W = h.W; a.p = h.p; a.D = D; a.N = N; a.P = m->P;
+    a.div_gw = sf::make_fastdiv(h.W / h.p); a.div_c = sf::make_fastdiv(h.C); a.div_p = sf::make_fastdiv(h.p);
     return sf::launch_head(a, s);
   });
 }

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 from gpu_util import host, torch  # noqa: E402
 from helpers import rel_l2  # noqa: E402
-from paper_2511_22009_amd import Model, Precision  # noqa: E402
+from paper_2511_22009_amd import Buffer, Model, Precision  # noqa: E402
 
 
 def _attention_model(heads, dh, H, Wd):
@@ -102,7 +102,7 @@ def test_gemm_fp32_tiles_and_ragged_k():
 def test_head_fp32(C, p, H, Wd, D, heads):
     """Final LayerNorm, modulate and output map alone (a network without blocks): patches of
     4 to 32 values, widths that fill no column step, token counts that end inside a
-    workgroup's 16 rows (and put each slot's rows elsewhere in it): against the oracle in 64
+    workgroup's four rows (and put each slot's rows elsewhere in it): against the oracle in 64
     bits, and every slot alone gives its bits in the batch."""
     import oracle
     cfg = W.Config("head", C=C, H=H, W=Wd, p=p, D=D, L=0, heads=heads, mlp=D, K=5, schedule="uniform5")
@@ -118,4 +118,72 @@ def test_head_fp32(C, p, H, Wd, D, heads):
     for k in range(5):
         assert rel_l2(got[k], oracle.forward_one(om, x[k], t[k], dtype=np.float64)) < 2e-6
         np.testing.assert_array_equal(host(m.velocity(put(x[k:k + 1]), t[k:k + 1]))[0], got[k])
+    m.close()
+
+
+def _fma(a, b, c):
+    """fp32 a * b + c with one rounding: the product is exact in 64 bits (whose own rounding of
+    the sum, then to 32 bits, misses the single rounding about once in 2^29)."""
+    return (a.astype(np.float64) * b.astype(np.float64) + c.astype(np.float64)).astype(np.float32)
+
+
+def _butterfly(x):
+    """Sum over the 64 lanes of the last axis by xor 32, 16, 8, 4, 2, 1."""
+    for d in (32, 16, 8, 4, 2, 1):
+        x = x + x[..., np.arange(64) ^ d]
+    return x[..., 0]
+
+
+def _head_in_order(h, table, W_f, b_f):
+    """The head in fp32 in its order of sums: h [rows, N, D], table [rows, 2D] (shift, scale)
+    -> [rows, N, P]. Lane l of a wavefront holds columns 4 (l + 64 i) .. + 3."""
+    R, N, D = h.shape
+    one, nv = np.float32(1.0), (D + 255) // 256
+
+    def lanes(a):  # [..., D] -> [..., nv, 64, 4], zeros past the end
+        out = np.zeros(a.shape[:-1] + (nv * 256,), np.float32)
+        out[..., :D] = a
+        return out.reshape(a.shape[:-1] + (nv, 64, 4))
+
+    def pairs(a, b):
+        return _fma(a[..., 0], b[..., 0], a[..., 1] * b[..., 1]) + _fma(a[..., 2], b[..., 2], a[..., 3] * b[..., 3])
+
+    v, live = lanes(h), lanes(np.ones(D, np.float32)) > 0
+    s = np.zeros((R, N, 64), np.float32)
+    for i in range(nv):
+        s = s + ((v[:, :, i, :, 0] + v[:, :, i, :, 1]) + (v[:, :, i, :, 2] + v[:, :, i, :, 3]))
+    d = v - (_butterfly(s) / np.float32(D))[..., None, None, None]
+    q = np.zeros((R, N, 64), np.float32)
+    for i in range(nv):
+        q = np.where(live[i, :, 0], q + pairs(d[:, :, i], d[:, :, i]), q)
+    rstd = one / np.sqrt(_butterfly(q) / np.float32(D) + np.float32(1e-6))
+    shift, scale = lanes(table[:, :D])[:, None], lanes(table[:, D:])[:, None]
+    y = np.where(live, _fma(d * rstd[..., None, None, None], one + scale, shift), np.float32(0.0))
+    w, out = lanes(W_f), np.empty((R, N, W_f.shape[0]), np.float32)
+    for f in range(W_f.shape[0]):
+        t = np.zeros((R, N, 64), np.float32)
+        for i in range(nv):
+            t = t + pairs(y[:, :, i], np.broadcast_to(w[f, i], y[:, :, i].shape))
+        out[..., f] = _butterfly(t) + b_f[f]
+    return out
+
+
+@pytest.mark.parametrize("prec", ["bf16", "fp32"])
+@pytest.mark.parametrize("C,p,H,Wd,D,heads", [(4, 2, 14, 22, 768, 12), (8, 2, 6, 10, 256, 4), (3, 2, 10, 6, 264, 3),
+                                              (1, 2, 20, 12, 1160, 29), (2, 4, 16, 8, 8, 1), (4, 2, 6, 2, 2048, 16)])
+def test_head_order_of_sums(C, p, H, Wd, D, heads, prec):
+    """The head's sums have one order, bit for bit: a stream step feeds its last bits back into
+    the queue, where they travel through the roundings of later steps."""
+    cfg = W.Config("head", C=C, H=H, W=Wd, p=p, D=D, L=0, heads=heads, mlp=D, K=3, schedule="uniform3")
+    tens = W.make_weights(cfg, init="tsens")
+    tens["pos"] = np.random.default_rng(14).standard_normal((cfg.N, D)).astype(np.float32)
+    m = Model(W.write_blob(cfg, tens), Precision[prec.upper()], 3)
+    x = W.latents(cfg, 3, seed=19)
+    t = np.random.default_rng(20).uniform(0.0, 1.0, 3).astype(np.float32)
+    got = host(m.velocity(torch.from_numpy(x).cuda(), t))
+    h = host(m.debug_read(Buffer.H, (3, cfg.N, D)))
+    table = host(m.debug_read(Buffer.TABLE, (3, 2 * D)))
+    ref = _head_in_order(h, table, np.asarray(tens["W_f"], np.float32), np.asarray(tens["b_f"], np.float32))
+    ref = ref.reshape(3, H // p, Wd // p, p, p, C).transpose(0, 5, 1, 3, 2, 4).reshape(got.shape)
+    np.testing.assert_array_equal(got, ref)
     m.close()
