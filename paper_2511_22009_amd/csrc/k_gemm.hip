@@ -19,6 +19,7 @@
 #include <cmath>
 
 #include "sf_device.h"
+#include "sf_tiles.h"
 
 namespace sf {
 
@@ -64,7 +65,8 @@ constexpr int batch_of(int n, int cap) {
 // outputs of a row per item. Items are processed in batches: every load of a batch (C
 // from LDS, bias, gate, residual) is issued before any of its results is used, with
 // out-of-tile items reading a clamped in-range address, so a batch pays one memory
-// latency instead of one per item. Only the stores are predicated.
+// latency instead of one per item. Only the stores are predicated. m0 is the first row of the
+// pass, which may lie past the matrix (loaded_row).
 template <EpiKind KIND, int BM, int BN, int NT>
 __device__ __forceinline__ void staged_epilogue(const GemmArgs& a, const float* Cs, int CP, int m0, int n0,
                                                 int tid) {
@@ -84,7 +86,7 @@ __device__ __forceinline__ void staged_epilogue(const GemmArgs& a, const float* 
       const int row = c / C4, c4 = c - row * C4;
       const int m = m0 + row, n = n0 + c4 * 4;
       ok[u] = (TOTAL % NT == 0 || c < TOTAL) && m < a.M && n < a.N;
-      mm[u] = ok[u] ? m : m0;
+      mm[u] = loaded_row(ok[u], m, m0, a.M);
       nn[u] = ok[u] ? n : 0;
       cv[u] = *(const float4*)&Cs[(ok[u] ? row : 0) * CP + (ok[u] ? c4 * 4 : 0)];
       bv[u] = *(const float4*)(a.bias + nn[u]);
@@ -140,7 +142,7 @@ struct ResItems {
     for (int u = 0; u < IT; ++u) {
       int row, c4, m, n;
       const bool ok = item(a, m0, n0, tid, u, row, c4, m, n);
-      const int mm = ok ? m : m0, nn = ok ? n : 0;
+      const int mm = loaded_row(ok, m, m0, a.M), nn = ok ? n : 0;
       b[u] = *(const float4*)(a.bias + nn);
       h[u] = *(const float4*)(a.h + (size_t)mm * a.ldh + nn);
       if constexpr (kGate) {

@@ -44,3 +44,22 @@ def test_short_context_guided_velocity_parity(name, prec):
     ref = oracle.velocity(oracle_model(name), x, t, ctx, nctx, cfg.guidance)
     errs = [rel_l2(got[k], ref[k]) for k in range(cfg.K)]
     assert max(errs) <= TOL[prec], errs
+
+
+@pytest.mark.parametrize("D,heads", [(1152, 16), (512, 8), (640, 10), (192, 4)])
+@pytest.mark.parametrize("H,Wd", [(2, 2), (4, 4), (8, 8)], ids=["n1", "n4", "n16"])
+def test_fewer_tokens_than_a_row_block(H, Wd, D, heads):
+    """One row of 1, 4 or 16 tokens in a model that holds one row: the gated residual
+    projections end inside the first of a tile's 32-row blocks, so later blocks lie past the
+    matrix and past the only row of the modulation table."""
+    from paper_2511_22009_amd import Model, Precision
+    cfg = W.Config("few", C=4, H=H, W=Wd, p=2, D=D, L=2, heads=heads, mlp=4 * D, K=1, schedule="uniform1")
+    blob = W.make_blob(cfg, init="tsens")
+    om = oracle.load_blob(blob)
+    x, t = W.latents(cfg, 1, seed=31), np.array([0.7], np.float32)
+    m = Model(blob, Precision.BF16, 1)
+    assert rel_l2(host(m.velocity(dev(x), t))[0], oracle.velocity(om, x, t)[0]) <= TOL_BF16
+    h = host(m.residual(dev(x), t, 2))[0]
+    ref, _ = oracle.residual_one(om, x[0], t[0], None, 2)
+    assert rel_l2(h, ref) <= TOL_BF16
+    m.close()
