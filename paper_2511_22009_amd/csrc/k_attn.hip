@@ -27,6 +27,7 @@
 // fp32 path (v_mfma_f32_16x16x4_f32): the same online softmax in fp32 throughout, described
 // at its kernel.
 #include "sf_device.h"
+#include "sf_rules.h"
 
 namespace sf {
 
@@ -99,8 +100,9 @@ __device__ __forceinline__ uint32_t max_pattern(const bf16x8 (&pf)[2]) {
 // lane holds one query and 16 keys of each block). The probabilities 2^(s - m2) are formed
 // against the current offsets first, added to lsum (SUM; otherwise the ones row of V^T sums
 // them in the MFMA) and rounded for P.V. Only if one of them reaches 2^64, or none of a
-// lane's reaches 2^-64 at the wavefront's first step (first: nothing accumulated yet), is
-// the block's step max (over both lane halves) looked at: its offset moves up to the max
+// lane's passes 2^-64 at the wavefront's first step (first: nothing accumulated yet), both
+// after rounding to bf16 (softmax_looks), is the block's step max (over both lane halves)
+// looked at: its offset moves up to the max
 // when that passes the offset by more than kOffSlack, and, at the first step, also down to
 // it when it lies more than kOffSlack below. The accumulated output (and row sum, SUM) are
 // rescaled when it moves, and the block's probabilities are formed again. Probabilities
@@ -110,15 +112,13 @@ __device__ __forceinline__ uint32_t max_pattern(const bf16x8 (&pf)[2]) {
 template <bool SUM, int QB, int DB>
 __device__ __forceinline__ void softmax_step_lazy(const f32x16 (&s)[QB], bool first, float (&m2)[QB],
                                                   float (&lsum)[QB], f32x16 (&o)[QB][DB], bf16x8 (&pf)[QB][2]) {
-  constexpr uint32_t k2p64 = 0x5F800000u, k2m64 = 0x1F800000u;  // 2^64 and 2^-64 in the high half
   float l[QB];
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) l[qb] = lsum[qb];
   wave_probs<SUM>(s, m2, l, pf);
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
-    const uint32_t top = max_pattern(pf[qb]);
-    if (__any(top >= k2p64 || (first && top < k2m64))) {
+    if (__any(softmax_looks(max_pattern(pf[qb]), first))) {
       float tmax = s[qb][0];
 #pragma unroll
       for (int e = 1; e < 16; ++e) tmax = fmaxf(tmax, s[qb][e]);

@@ -19,7 +19,7 @@
 #include <cmath>
 
 #include "sf_device.h"
-#include "sf_tiles.h"
+#include "sf_rules.h"
 
 namespace sf {
 

@@ -75,7 +75,8 @@ def test_block0_intermediates(name, prec):
 
 
 @pytest.mark.parametrize("HW", [(32, 64), (10, 12), (8, 8)], ids=["512tok", "30tok", "16tok"])
-@pytest.mark.parametrize("D,heads", [(128, 2), (144, 2), (96, 2), (64, 2)], ids=["dh64", "dh72", "dh48", "dh32"])
+@pytest.mark.parametrize("D,heads", [(128, 2), (144, 2), (96, 2), (64, 2), (48, 2), (208, 2), (240, 2), (256, 2)],
+                         ids=["dh64", "dh72", "dh48", "dh32", "dh24", "dh104", "dh120", "dh128"])
 def test_attention_scores_far_from_zero(D, heads, HW):
     """Scores whose level per query lies far outside [-64, 64] in exp2 units, on both
     sides: every key entry is 128 plus a small exact integer step, so a query's scores are
