@@ -22,12 +22,15 @@ constexpr int kGemvSamples = 4;  // samples per pass (inputs held in registers)
 // X, or built as the sinusoids of 1000 t). The RW x 4 row/sample partial sums leave
 // through butterfly reductions of 16 values. One task (RW rows) per wavefront.
 // MANY: more than one pass of four samples. The weights are then loaded once, ahead of the
-// passes (56832 x 768 bf16 weights, 87 MB, 8 samples: 36.1 us with a load per pass, 31.2
-// so, 16 samples 63.5 and 47.8); a single pass keeps its own loads, whose registers it
-// shares with the inputs' (4 samples: 20.0 us, 23.0 with the form for many).
+// passes (56832 x 768 bf16 weights, 87 MB, 8 samples: 32.2 us with a load per pass, 30.1
+// so, 16 samples 59.6 and 47.7); the form for a single pass issues them together with the
+// inputs (1536 x 1536 fp32, 4 samples 6.7 us). The sinusoid mode takes a load per pass
+// whatever the count: its weights are few and its barriers lie in the loop (5 to 16 samples
+// 5.6 to 10.2 us, with the weights ahead of it 6.0 to 12).
 template <typename WT, int NC, int RW, int XMODE, bool MANY>
 __device__ __forceinline__ void gemv_body(const GemvArgs& a, int bid) {
   constexpr int E = 16 / sizeof(WT);  // elements per 16-byte chunk
+  static_assert(XMODE == 0 || !MANY, "the sinusoids' barriers lie in the loop over passes");
   static_assert(RW * kGemvSamples % 16 == 0, "rows x samples must fill butterfly groups");
   const int lane = threadIdx.x & 63;
   const int j0 = (bid * 4 + (threadIdx.x >> 6)) * RW;
@@ -38,8 +41,7 @@ __device__ __forceinline__ void gemv_body(const GemvArgs& a, int bid) {
   const int nchunk = a.K / E;
   const __amdgpu_buffer_rsrc_t w_src = buffer_rsrc(a.W, (uint32_t)((size_t)a.R * a.K * sizeof(WT)));
   const __amdgpu_buffer_rsrc_t x_src = buffer_rsrc(a.X, a.X ? (uint32_t)((size_t)a.B * a.ldx * 4) : 0u);
-  u32x4 w[RW][NC];
-  auto load_w = [&]() __attribute__((always_inline)) {
+  auto load_w = [&](u32x4 (&w)[RW][NC]) __attribute__((always_inline)) {
 #pragma unroll
     for (int rr = 0; rr < RW; ++rr) {
       const int j = min(j0 + rr, a.R - 1);
@@ -50,22 +52,8 @@ __device__ __forceinline__ void gemv_body(const GemvArgs& a, int bid) {
       }
     }
   };
-  if (MANY) load_w();
-  for (int b0 = 0; b0 < (MANY ? a.B : 1); b0 += kGemvSamples) {
-    const int nb = min(kGemvSamples, a.B - b0);
-    if constexpr (XMODE == 1) {
-      // [cos | sin] of 1000 t times the frequency table, for this batch's samples
-      const int half = a.K >> 1;
-      __syncthreads();
-      for (int i = threadIdx.x; i < nb * a.K; i += blockDim.x) {
-        const int bb = i / a.K, k = i - bb * a.K;
-        const int f = k < half ? k : k - half;
-        const float phi = (1000.0f * a.t.v[b0 + bb]) * a.freqs[f];
-        emb[i] = k < half ? cosf(phi) : sinf(phi);
-      }
-      __syncthreads();
-    }
-    if (!MANY) load_w();
+  // four samples, b0 on, against rows held in w
+  auto pass = [&](const u32x4 (&w)[RW][NC], int b0, int nb) __attribute__((always_inline)) {
     float x[kGemvSamples][NC][E];
 #pragma unroll
     for (int bb = 0; bb < kGemvSamples; ++bb)
@@ -129,11 +117,47 @@ __device__ __forceinline__ void gemv_body(const GemvArgs& a, int bid) {
         a.Y[(size_t)(b0 + bb) * a.ldy + j] = sum;
       }
     }
+  };
+  if constexpr (MANY) {
+    u32x4 w[RW][NC];
+    load_w(w);
+    for (int b0 = 0; b0 < a.B; b0 += kGemvSamples) pass(w, b0, min(kGemvSamples, a.B - b0));
+  } else {
+    for (int b0 = 0; b0 < a.B; b0 += kGemvSamples) {
+      const int nb = min(kGemvSamples, a.B - b0);
+      if constexpr (XMODE == 1) {
+        // [cos | sin] of 1000 t times the frequency table, for this batch's samples
+        const int half = a.K >> 1;
+        __syncthreads();
+        for (int i = threadIdx.x; i < nb * a.K; i += blockDim.x) {
+          const int bb = i / a.K, k = i - bb * a.K;
+          const int f = k < half ? k : k - half;
+          const float phi = (1000.0f * a.t.v[b0 + bb]) * a.freqs[f];
+          emb[i] = k < half ? cosf(phi) : sinf(phi);
+        }
+        __syncthreads();
+      }
+      u32x4 w[RW][NC];
+      load_w(w);
+      pass(w, b0, nb);
+    }
   }
 }
 
+// Wavefronts per SIMD that the register budget allows for. The form for many samples with four
+// or more fp32 chunks per lane holds 64 to 128 weights and as many inputs; left to itself the
+// compiler keeps 96 to 170 registers, fetches the inputs a few at a time, and the timestep
+// MLP's second layer, whose few workgroups hide nothing, waits for each: 8 samples of width
+// 1024 / 1536 / 2048 11.9 / 16.0 / 19.7 us, so 5.8 / 6.8 / 8.8 (a load per pass 8.2 / 11.0 /
+// 16.3).
+template <typename WT, int NC, bool MANY>
+constexpr int gemv_waves_per_simd() {
+  return MANY && sizeof(WT) == 4 && NC >= 4 ? 2 : 8;
+}
+
 template <typename WT, int NC, int RW, int XMODE, bool MANY>
-__global__ __launch_bounds__(256) void gemv_kernel(GemvArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, gemv_waves_per_simd<WT, NC, MANY>())))
+void gemv_kernel(GemvArgs a) {
   gemv_body<WT, NC, RW, XMODE, MANY>(a, blockIdx.x);
 }
 
@@ -149,17 +173,11 @@ template <typename WT, int NC>
 static void launch_gemv_nc(const GemvArgs& a, hipStream_t s) {
   constexpr int RW = gemv_rows_per_wave<WT, NC>();
   const int tasks = (a.R + RW - 1) / RW;
-  const bool many = a.B > kGemvSamples;
   const dim3 grid((tasks + 3) / 4);
   if (a.x_mode == 1) {
     // the sinusoids feed the fp32 timestep layer only
-    if constexpr (sizeof(WT) == 4) {
-      if (many)
-        launch((gemv_kernel<WT, NC, RW, 1, true>), grid, dim3(256), 0, s, a);
-      else
-        launch((gemv_kernel<WT, NC, RW, 1, false>), grid, dim3(256), 0, s, a);
-    }
-  } else if (many) {
+    if constexpr (sizeof(WT) == 4) launch((gemv_kernel<WT, NC, RW, 1, false>), grid, dim3(256), 0, s, a);
+  } else if (a.B > kGemvSamples) {
     launch((gemv_kernel<WT, NC, RW, 0, true>), grid, dim3(256), 0, s, a);
   } else {
     launch((gemv_kernel<WT, NC, RW, 0, false>), grid, dim3(256), 0, s, a);

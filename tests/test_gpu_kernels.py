@@ -7,7 +7,7 @@ import pytest
 import oracle
 import workloads as W
 from conftest import oracle_model
-from helpers import rel_l2
+from helpers import bf16_round, rel_l2
 
 pytestmark = pytest.mark.gpu
 
@@ -113,4 +113,28 @@ def test_attention_scores_far_from_zero(D, heads, HW):
     errs = [rel_l2(full[r], oracle.attention(flat(q64[r]), flat(k64[r]), flat(v64[r]), heads)) for r in range(R)]
     assert max(errs) <= ISO["bf16"], max(errs)
     np.testing.assert_array_equal(full[:4], part)
+    m.close()
+
+
+@pytest.mark.parametrize("prec", ["bf16", "fp32"])
+@pytest.mark.parametrize("D,heads", [(64, 1), (264, 3), (520, 5), (1032, 43), (1544, 193), (2048, 32)])
+def test_modulation_of_many_samples(D, heads, prec):
+    """One, four, five and nine samples in a call (one pass over the weights' rows, or several
+    with the rows held) give each sample the bits it has alone, at widths of one to eight
+    16-byte chunks per lane, and the table of 64-bit sums: fp32 sums of at most 2048 products
+    behind two layers whose rounding passes through the sinusoids' phases, 4e-6."""
+    from paper_2511_22009_amd import Model, Precision
+    cfg = W.Config("mod", C=4, H=4, W=4, p=2, D=D, L=0, heads=heads, mlp=64)
+    blob = W.make_blob(cfg, init="tsens")
+    m = Model(blob, Precision[prec.upper()], 9)
+    t = np.random.default_rng(3).uniform(0.0, 1.0, 9).astype(np.float32)
+    full = host(m.modulation(t))
+    for n in (1, 4, 5):
+        np.testing.assert_array_equal(host(m.modulation(t[:n])), full[:n])
+    np.testing.assert_array_equal(host(m.modulation(t[8:])), full[8:])
+    om = oracle.load_blob(blob)
+    if prec == "bf16":
+        om.top["W_fmod"] = bf16_round(om.top["W_fmod"])
+    ref = np.stack([oracle.modulation_table(om, t[k], dtype=np.float64).reshape(-1) for k in range(9)])
+    assert rel_l2(full, ref) <= 4e-6
     m.close()
