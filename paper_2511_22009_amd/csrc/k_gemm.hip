@@ -374,8 +374,11 @@ __device__ __forceinline__ void bf16_epilogue(const GemmArgs& a, const f32x16 (&
 // reused from one L2. Bijective for any tile count and group size. Eight rows, but four
 // where that measured faster: the register-staged tiles of the QKV projection on grids of
 // at least 64 tile rows or at most 8 tile columns and of the MLP up-projection on at least
-// 64, and the 128 x 96 tiles of the narrow projections other than the MLP down-projection
-// on at least 64.
+// 64; the directly staged tiles whose K slice is split over wavefronts, other than for the
+// MLP down-projection, on at least 64; and 128 x 192 with the fragments ahead on at least 64 tile
+// rows and 10 tile columns (16384 x 2304 x 768 68.0 us with eight, 63.4 with four, 16384 x 4608 x
+// 1152 174.8 and 171.3, 8192 x 2048 x 2048 103.2 and 90.4; with six columns, 16384 x 1152 x 4608,
+// 167.4 and 175.5). 128 x 128 with the fragments ahead is level (0.98 to 1.02).
 constexpr int kXcds = 8;
 constexpr int kGroupM = 8;
 __device__ __forceinline__ void tile_coords(int nbm, int nbn, int& mt, int& nt, int GM = kGroupM) {
@@ -414,13 +417,11 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_sched_kernel(GemmArgs 
   constexpr int ACH = (ATOT + NT - 1) / NT;
   constexpr int BCH = (BTOT + NT - 1) / NT;
   constexpr int AB_BYTES = 2 * (BM + BN) * LDK * 2 + 16;  // + spare slot
+  constexpr bool kBf16Out = KIND == EPI_GELU || KIND == EPI_QKV || KIND == EPI_KVX;
   constexpr int CP = BN + 4;
-  constexpr int LDS_CAP = 160 * 1024;
-  constexpr int NP = (BM * CP * 4 <= LDS_CAP) ? 1 : ((BM / 2) * CP * 4 <= LDS_CAP ? 2 : 4);
-  constexpr int RP = BM / NP;
-  constexpr int C_BYTES = RP * CP * 4;
+  constexpr int C_BYTES = kBf16Out ? 0 : BM * CP * 4;  // the fp32 tile of the residual epilogues
   constexpr int SMEM = AB_BYTES > C_BYTES ? AB_BYTES : C_BYTES;
-  static_assert(SMEM <= LDS_CAP, "tile does not fit in LDS");
+  static_assert(SMEM <= 160 * 1024, "tile does not fit in LDS");
   static_assert(BM * (BN + kEpiPad) * 2 <= SMEM, "staged bf16 tile does not fit in LDS");
   constexpr int KS = BK / 16;                 // MFMA K steps per tile
   constexpr int NMFMA = TM * TN * KS;
@@ -445,7 +446,6 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_sched_kernel(GemmArgs 
   const int m0 = mt * BM, n0 = nt * BN;
   if (!tile_live<KIND, BM>(a, m0)) return;  // uniform across the workgroup
   // the tile's bias columns go to LDS now, so the epilogue does not wait on them
-  constexpr bool kBf16Out = KIND == EPI_GELU || KIND == EPI_QKV || KIND == EPI_KVX;
   __shared__ __attribute__((aligned(16))) float bias_s[kBf16Out ? BN : 4];
   if constexpr (kBf16Out) {
     for (int c = tid; c < BN / 4; c += NT) {
@@ -597,23 +597,16 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_sched_kernel(GemmArgs 
   } else {
     float* Cs = (float*)smem;
 #pragma unroll
-    for (int p = 0; p < NP; ++p) {
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int rb0 = (wm * TM + i) * 32;
-        if (rb0 < p * RP || rb0 >= (p + 1) * RP) continue;
+      for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-            *(f32x4*)&Cs[(rb0 - p * RP + l32) * CP + (wn * TN + j) * 32 + q * 8 + g * 4] = v;
-          }
-      }
-      __syncthreads();
-      staged_epilogue<KIND, RP, BN, NT>(a, Cs, CP, m0 + p * RP, n0, tid);
-      if (p + 1 < NP) __syncthreads();
-    }
+        for (int q = 0; q < 4; ++q) {
+          const f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+          *(f32x4*)&Cs[((wm * TM + i) * 32 + l32) * CP + (wn * TN + j) * 32 + q * 8 + g * 4] = v;
+        }
+    __syncthreads();
+    staged_epilogue<KIND, BM, BN, NT>(a, Cs, CP, m0, n0, tid);
   }
 }
 
@@ -972,7 +965,7 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void gemm_bf16_pipe_kernel(Gemm
   int mt, nt;
   {
     const int nbm = (a.M + BM - 1) / BM, nbn = (a.N + BN - 1) / BN;
-    tile_coords(nbm, nbn, mt, nt);
+    tile_coords(nbm, nbn, mt, nt, BN == 192 && !HALVES && nbm >= 64 && nbn >= 10 ? 4 : kGroupM);
   }
   const int m0 = mt * BM, n0 = nt * BN;
   if (!tile_live<KIND, BM>(a, m0)) return;  // uniform across the workgroup
@@ -1350,118 +1343,46 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_f32_kernel(GemmArgs a) {
 // Directly staged with the fragments read a K step ahead (LDS stages, wavefronts per
 // SIMD, both halves of a K slice summed apart).
 #define SF_GEMM_PIPE_TILES(X)                             \
-  X(kPipe256x192, 256, 192, 4, 2, 2, 2, false)            \
   X(kPipe128x192, 128, 192, 2, 2, 2, 2, false)            \
   X(kPipe128, 128, 128, 2, 2, 2, 2, false)                \
   X(kPipe64, 64, 64, 2, 2, 4, 2, false)                   \
   X(kPipeHalf128x192, 128, 192, 4, 2, 3, 2, true)         \
   X(kPipeHalf128, 128, 128, 2, 2, 2, 2, true)
 
-enum GemmTile {
-  kTile128, kTile128x288, kTile256x192, kHalf128x96, kHalf128, kHalf64, kPipe256x192, kPipe128x192, kPipe128, kPipe64, kPipeHalf128x192, kPipeHalf128
-};
-
 template <EpiKind KIND>
-static hipError_t launch_bf16_tile(int tile, const GemmArgs& a, hipStream_t s) {
+static hipError_t launch_bf16_tile(GemmTile tile, const GemmArgs& a, hipStream_t s) {
+#define SF_LAUNCH(kernel, bm, bn, waves) \
+  launch(kernel, dim3(((a.N + bn - 1) / bn) * ((a.M + bm - 1) / bm)), dim3((waves)*64), 0, s, a)
   switch (tile) {
-#define SF_TILE_CASE(id, bm, bn, bk, wm, wn)                                                       \
-  case id:                                                                                         \
-    launch((gemm_bf16_sched_kernel<bm, bn, bk, wm, wn, KIND>),                                     \
-           dim3(((a.N + bn - 1) / bn) * ((a.M + bm - 1) / bm)), dim3(wm * wn * 64), 0, s, a);      \
+#define SF_TILE_CASE(id, bm, bn, bk, wm, wn)                                                         \
+  case id:                                                                                           \
+    if constexpr (gemm_tile_used(id, KIND))                                                          \
+      SF_LAUNCH((gemm_bf16_sched_kernel<bm, bn, bk, wm, wn, KIND>), bm, bn, wm* wn);                 \
+    else                                                                                             \
+      return hipErrorInvalidValue;                                                                   \
     break;
     SF_GEMM_TILES(SF_TILE_CASE)
 #undef SF_TILE_CASE
-#define SF_DMA_TILE_CASE(id, bm, bn, bk, wm, wn, ks, st)                                           \
-  case id:                                                                                         \
-    launch((gemm_bf16_dma_kernel<bm, bn, bk, wm, wn, ks, st, KIND>),                               \
-           dim3(((a.N + bn - 1) / bn) * ((a.M + bm - 1) / bm)), dim3(wm * wn * ks * 64), 0, s, a); \
+#define SF_DMA_TILE_CASE(id, bm, bn, bk, wm, wn, ks, st)                                             \
+  case id:                                                                                           \
+    SF_LAUNCH((gemm_bf16_dma_kernel<bm, bn, bk, wm, wn, ks, st, KIND>), bm, bn, wm* wn* ks);         \
     break;
     SF_GEMM_DMA_TILES(SF_DMA_TILE_CASE)
 #undef SF_DMA_TILE_CASE
-#define SF_PIPE_TILE_CASE(id, bm, bn, wm, wn, st, mw, hv)                                          \
-  case id:                                                                                         \
-    launch((gemm_bf16_pipe_kernel<bm, bn, wm, wn, st, mw, hv, KIND>),                              \
-           dim3(((a.N + bn - 1) / bn) * ((a.M + bm - 1) / bm)), dim3(wm * wn * 64), 0, s, a);      \
+#define SF_PIPE_TILE_CASE(id, bm, bn, wm, wn, st, mw, hv)                                        \
+  case id:                                                                                           \
+    if constexpr (gemm_tile_used(id, KIND))                                                          \
+      SF_LAUNCH((gemm_bf16_pipe_kernel<bm, bn, wm, wn, st, mw, hv, KIND>), bm, bn, wm* wn);      \
+    else                                                                                             \
+      return hipErrorInvalidValue;                                                                   \
     break;
     SF_GEMM_PIPE_TILES(SF_PIPE_TILE_CASE)
 #undef SF_PIPE_TILE_CASE
     default:
       return hipErrorInvalidValue;
   }
+#undef SF_LAUNCH
   return hipGetLastError();
-}
-
-// Which tile. A row's result must not depend on how many rows are in the batch, so the
-// order in which K is summed follows from N alone: outputs up to 768 wide that are whole
-// multiples of 96 or 128 (the attention output and MLP down-projections of the narrower
-// networks) sum the two halves of every 64-wide slice apart and add them at the end,
-// everything else sums K in one go; within each of the two families every tile gives the
-// same bits, and M may choose. All times below are microseconds of one launch.
-//
-// Halves (4096 x 768: one 128 x 96 tile per CU; eight wavefronts hide the loads):
-//   * 64 x 64 while that is at most one and a half workgroups per CU: 1024 x 768 x 3072
-//     12.6 against 21.7 with 128 x 96, 2048 x 768 x 3072 22.8 against 23.1, but 2760 x 768 x
-//     3072 32.4 against 26.0 (up to two per CU where the alternative is 128 x 128:
-//     4096 x 512 x 2048 18.8 against 19.9);
-//   * 128 x 192, each wavefront holding both halves' sums, once it gives every CU a
-//     workgroup: it moves 28 % fewer operand bytes per output, and the loads are what binds
-//     these (8192 x 768 x 3072 49.8 against 56.0, 16384 x 768 x 3072 99 against 120);
-//   * 128 x 96, or for other multiples of 128 the 128 x 128 forms: both halves in each
-//     wavefront, two workgroups per CU, from one and a half per CU on (16384 x 512 x 2048
-//     44.6 against 48.1), else split over wavefronts (8192 x 512 x 2048 27.1 against 31.4).
-//
-// One go: 64 x 64 while that is at most one and a half workgroups per CU (1024 x 1152 x 4608
-// 28.5 against 37.8 with 128 x 128, 256 x 3072 x 768 5.5 against 9.3; 1024 x 2304 x 768, more
-// than two per CU, 13.1 against 11.1). Above, the tile with the least work on its busiest
-// CU: k = the most tiles a CU gets, times what a tile costs, relative to 128 x 128 tiles, as
-// fitted to launches of 1024 to 16384 rows (K 768 and 1152):
-//   * 128 x 128, register-staged: 11 for one, 8.9 k for more. Directly staged with the
-//     fragments ahead: 12 and 8.8 k (4096 x 1152 x 4608 61 against 72, 16384 x 3456 x 1152
-//     144 against 148; not for the GELU epilogue, 60 against 58 at 4096 x 4608 x 1152);
-//   * 128 x 192 with two workgroups per CU, one's main loop over the other's epilogue:
-//     18 and 12 k (4096 x 4608 x 1152 53 against 58, 16384 x 1152 x 4608 185 against 206);
-//   * 256 x 192, one workgroup per CU and the fewest operand bytes: 23.3 k (16384 x 2304 x
-//     768 68.6 against 73.6 with 128 x 192 and 78.9 with 128 x 128), 24.2 k where the GELU
-//     epilogue follows it more than once (16384 x 4608 x 1152 196 against 186);
-//   * 128 x 288, register-staged by twelve wavefronts, 22 for one and never more, for the
-//     QKV projection only: it fills the chip where 256 x 192 leaves a quarter of it idle (4096 x
-//     2304 x 768, in the step: 21.9 against 22.7);
-//   * 256 x 192, register-staged, 23 for one and never more, for the GELU epilogue: level alone
-//     (4096 x 3072 x 768 25.6 against 25.4), but the four-slot 512^2 step took 0.994 to 0.997 of
-//     its time before these tiles with it, 1.011 to 1.017 with the other one (1.000 on one GPU).
-int choose_gemm_tile(int M, int N, EpiKind kind) {
-  auto tiles = [&](int bm, int bn) { return (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-  constexpr long kCUs = 256;
-  const long small = tiles(64, 64);
-  if (N <= 768 && (N % 96 == 0 || N % 128 == 0)) {
-    if (2 * small <= 3 * kCUs) return kHalf64;
-    if (N % 192 == 0 && tiles(128, 192) >= kCUs) return kPipeHalf128x192;
-    if (N % 96 == 0) return kHalf128x96;
-    if (small <= 2 * kCUs) return kHalf64;
-    return 2 * tiles(128, 128) >= 3 * kCUs ? kPipeHalf128 : kHalf128;
-  }
-  if (2 * small <= 3 * kCUs) return kPipe64;
-  auto most = [&](int bm, int bn) { return (float)((tiles(bm, bn) + kCUs - 1) / kCUs); };
-  const float k128 = most(128, 128), k192 = most(128, 192), k256 = most(256, 192);
-  int best = kTile128;
-  float cost = k128 > 1 ? 8.9f * k128 : 11.0f;
-  auto take = [&](int tile, float c) {
-    if (c < cost) {
-      best = tile;
-      cost = c;
-    }
-  };
-  if (kind != EPI_GELU) take(kPipe128, k128 > 1 ? 8.8f * k128 : 12.0f);
-  take(kPipe128x192, k192 > 1 ? 12.0f * k192 : 18.0f);
-  take(kPipe256x192, (kind == EPI_GELU && k256 > 1 ? 24.2f : 23.3f) * k256);
-  if (kind == EPI_QKV && tiles(128, 288) <= kCUs) take(kTile128x288, 22.0f);
-  if (kind == EPI_GELU && k256 == 1) take(kTile256x192, 23.0f);
-  return best;
-}
-
-int choose_gemm_f32_tile(int M, int N) {
-  auto tiles = [&](int bm, int bn) { return (size_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-  return tiles(64, 64) >= 512 ? 0 : 1;
 }
 
 template <EpiKind KIND>
@@ -1481,25 +1402,21 @@ static hipError_t launch_f32_tile(int tile, const GemmArgs& a, hipStream_t s) {
 }
 
 template <EpiKind KIND>
-static hipError_t launch_kind(bool use_bf16, int tile, const GemmArgs& a, hipStream_t s) {
-  if (use_bf16) return launch_bf16_tile<KIND>(tile < 0 ? choose_gemm_tile(a.M, a.N, KIND) : tile, a, s);
-  return launch_f32_tile<KIND>(tile < 0 ? choose_gemm_f32_tile(a.M, a.N) : tile, a, s);
-}
-
-hipError_t launch_gemm_tile(bool use_bf16, int tile, EpiKind kind, const GemmArgs& a, hipStream_t s) {
-  switch (kind) {
-    case EPI_QKV: return launch_kind<EPI_QKV>(use_bf16, tile, a, s);
-    case EPI_RES_GATE: return launch_kind<EPI_RES_GATE>(use_bf16, tile, a, s);
-    case EPI_GELU: return launch_kind<EPI_GELU>(use_bf16, tile, a, s);
-    case EPI_RES: return launch_kind<EPI_RES>(use_bf16, tile, a, s);
-    case EPI_RES_GATE_MLP: return launch_kind<EPI_RES_GATE_MLP>(use_bf16, tile, a, s);
-    case EPI_KVX: return launch_kind<EPI_KVX>(use_bf16, tile, a, s);
-  }
-  return hipErrorInvalidValue;
+static hipError_t launch_kind(bool use_bf16, const GemmArgs& a, hipStream_t s) {
+  if (use_bf16) return launch_bf16_tile<KIND>(choose_gemm_tile(a.M, a.N, KIND), a, s);
+  return launch_f32_tile<KIND>(choose_gemm_f32_tile(a.M, a.N), a, s);
 }
 
 hipError_t launch_gemm(bool use_bf16, EpiKind kind, const GemmArgs& a, hipStream_t s) {
-  return launch_gemm_tile(use_bf16, -1, kind, a, s);
+  switch (kind) {
+    case EPI_QKV: return launch_kind<EPI_QKV>(use_bf16, a, s);
+    case EPI_RES_GATE: return launch_kind<EPI_RES_GATE>(use_bf16, a, s);
+    case EPI_GELU: return launch_kind<EPI_GELU>(use_bf16, a, s);
+    case EPI_RES: return launch_kind<EPI_RES>(use_bf16, a, s);
+    case EPI_RES_GATE_MLP: return launch_kind<EPI_RES_GATE_MLP>(use_bf16, a, s);
+    case EPI_KVX: return launch_kind<EPI_KVX>(use_bf16, a, s);
+  }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace sf

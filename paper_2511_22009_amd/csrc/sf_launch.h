@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "sf_rules.h"
+
 namespace sf {
 
 // Events that the next kernel launched from this host thread attaches to its own
@@ -149,16 +151,6 @@ struct HeadArgs {
 hipError_t launch_head(const HeadArgs& a, hipStream_t s);
 
 // ---- K3: GEMM  C[M][N] = A[M][K] . B[N][K]^T with a fused epilogue -----------------
-enum EpiKind {
-  EPI_QKV = 0,       // + bias, scatter to head-major q / k and transposed v
-  EPI_RES_GATE = 1,  // h += gate[slot][n] * (acc + bias)
-  EPI_GELU = 2,      // out = GELU_tanh(acc + bias)
-  EPI_RES = 3,       // h += acc + bias
-  EPI_RES_GATE_MLP = 4, // EPI_RES_GATE for the MLP down-projection (a separate kernel
-                        // symbol, so profiles tell it from the attention projection)
-  EPI_KVX = 5           // + bias, the context keys / transposed values of every block:
-                        // column n is block (n / D) / 2, key if (n / D) even else value
-};
 struct GemmArgs {
   const void* A;
   int lda;
@@ -188,9 +180,6 @@ struct GemmArgs {
   int ldo;
 };
 hipError_t launch_gemm(bool use_bf16, EpiKind kind, const GemmArgs& a, hipStream_t s);
-// The same with an explicit bf16 tile shape (index into the tile table; -1 = choose).
-hipError_t launch_gemm_tile(bool use_bf16, int tile, EpiKind kind, const GemmArgs& a, hipStream_t s);
-int choose_gemm_tile(int M, int N, EpiKind kind);
 
 // ---- K4: softmax attention per (network row, head) ---------------------------------
 // Column of key t in the permuted transposed-v layout: bits 2 and 3 of t swapped, so in

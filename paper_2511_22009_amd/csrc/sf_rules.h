@@ -5,6 +5,108 @@
 
 namespace sf {
 
+// Epilogues of the projections.
+enum EpiKind {
+  EPI_QKV = 0,       // + bias, scatter to head-major q / k and transposed v
+  EPI_RES_GATE = 1,  // h += gate[slot][n] * (acc + bias)
+  EPI_GELU = 2,      // out = GELU_tanh(acc + bias)
+  EPI_RES = 3,       // h += acc + bias
+  EPI_RES_GATE_MLP = 4, // EPI_RES_GATE for the MLP down-projection (a separate kernel
+                        // symbol, so profiles tell it from the attention projection)
+  EPI_KVX = 5           // + bias, the context keys / transposed values of every block:
+                        // column n is block (n / D) / 2, key if (n / D) even else value
+};
+
+// Tiles of the bf16 projections; what each is stands at its kernel.
+enum GemmTile {
+  kTile128, kTile128x288, kTile256x192,                                   // register-staged
+  kHalf128x96, kHalf128, kHalf64,                                         // K slice split over wavefronts
+  kPipe128x192, kPipe128, kPipe64, kPipeHalf128x192, kPipeHalf128        // fragments a K step ahead
+};
+
+// Whether the sums over K take the two halves of every 64-wide slice apart and add them at
+// the end. It follows from N alone, as a row's result must not depend on how many rows are
+// in the batch: outputs up to 768 wide that are whole multiples of 96 or 128 (the attention
+// output and MLP down-projections of the narrower networks). All tiles of one family give the
+// same bits, and M may choose among them.
+constexpr bool sums_halves(int N) { return N <= 768 && (N % 96 == 0 || N % 128 == 0); }
+
+// Whether a tile of the table is ever chosen for an epilogue (only these are compiled).
+constexpr bool gemm_tile_used(GemmTile tile, EpiKind kind) {
+  return tile == kTile256x192 ? kind == EPI_GELU : tile != kPipe128 || kind != EPI_GELU;
+}
+
+// Which tile: the one with the least work on its busiest CU. A CU gets k = tiles / 256 of
+// them, rounded up. A tile whose LDS leaves room for one workgroup per CU costs a fixed
+// amount each; of the smaller ones two run side by side, so they cost so much per pair and,
+// where k is odd, a last one that has the CU for itself. That last one is dear where only the
+// other workgroup hides the loads: 128 x 128 with the fragments ahead takes 0.85 to 0.98 of
+// the register-staged one's time at even k and 1.03 to 1.24 at odd k.
+//
+// Costs are relative, fitted to launches of all four projections of one-block networks: 22
+// widths from 64 to 2048 (N to 8192, K to 8192) at 256 to 16384 rows, 968 of them. The rule's
+// choice takes 1.004 of the fastest tile's time on average, 1.2 in the worst case; choosing by
+// k alone and by a threshold for the short ones took 1.021 and 1.6. Some times (us per
+// launch, rows x N x K):
+//   * 64 x 64: 2048 x 1024 x 4096 26.6, the next best 34.8 (128 x 128); 2048 x 896 x 896 11.8
+//     and 15.3; 1024 x 2304 x 768, more than two per CU, 13.1 and 11.1.
+//   * 128 x 128, register-staged, against fragments ahead: 12288 x 1024 x 4096 (k = 3) 107.6
+//     and 121.4, 8192 x 1024 x 1024 (k = 2) 33.4 and 28.4. Not the latter for the GELU
+//     epilogue: 12288 x 2304 x 576 45.7 and 51.0.
+//   * 128 x 192 against 128 x 128: 16384 x 2304 x 768 63.4 and 70.8, 16384 x 4608 x 1152 171
+//     and 182, 8192 x 1152 x 1152 35.8 and 39.3. Below K = 600 the GELU epilogue
+//     weighs more: 16384 x 1792 x 448 44.0 and, 128 x 128, 40.0. (256 x 192 with the fragments
+//     ahead: 69.8 and 182, at 4096 rows 22.1 against 22.3 at N 2304; not kept.)
+//   * 128 x 288 and, for the GELU epilogue, 256 x 192, both register-staged with one workgroup
+//     per CU, where one round of them holds everything. 128 x 288 against 128 x 192: 4096 x
+//     2304 x 768 22.2 and 22.3 (in the four-slot step 21.9 and 22.7), 8192 x 1152 x 384 16.2
+//     and 16.6, 4096 x 2112 x 704 20.4 and 21.1, 8192 x 1152 x 4608 88.7 and 91.2, but 2048 x
+//     4608 x 1536 35.4 and 34.6. 256 x 192: 4096 x 3072 x 768 25.1, 3072 x 3840 x 960 27.5,
+//     2048 x 6144 x 1536 39.2 and 40.4.
+//   * halves: 64 x 64 up to two per CU: 2048 x 768 x 768 9.7 and, 128 x 96, 11.3; 4096 x 512 x
+//     512 9.2 and 10.6. Beyond, 128 x 96 4096 x 768 x 3072 24.8, the next 25.8 (128 x 128
+//     split); 128 x 192 with both halves in a wavefront 8192 x 768 x 768 21.6 and, 128 x 96,
+//     23.2, but 12288 x 768 x 768 (1.5 rounds of it) 33.8 and 32.2; 128 x 128 12288 x 576 x 576
+//     21.7 with both halves in a wavefront, 22.8 split, 25.5 with 128 x 96, 29.8 with 128 x 192.
+inline GemmTile choose_gemm_tile(int M, int N, EpiKind kind) {
+  constexpr long kCUs = 256;
+  auto tiles = [&](int bm, int bn) { return ((long)M + bm - 1) / bm * (((long)N + bn - 1) / bn); };
+  auto most = [&](int bm, int bn) { return (tiles(bm, bn) + kCUs - 1) / kCUs; };
+  auto pairs = [](long k, long pair, long last) { return k / 2 * pair + k % 2 * last; };
+  long cost = -1;
+  GemmTile best = kTile128;
+  auto take = [&](GemmTile tile, long c) {
+    if (cost < 0 || c < cost) {
+      best = tile;
+      cost = c;
+    }
+  };
+  const long k64 = most(64, 64), k128 = most(128, 128), k192 = most(128, 192);
+  if (sums_halves(N)) {
+    if (tiles(64, 64) <= 2 * kCUs) return kHalf64;
+    take(kHalf64, pairs(k64, 121, 74));
+    take(kHalf128x96, 100 * most(128, 96));
+    take(kPipeHalf128x192, 156 * k192);
+    take(kHalf128, 125 * k128);
+    take(kPipeHalf128, pairs(k128, 190, 126));
+    return best;
+  }
+  const bool gelu = kind == EPI_GELU;
+  take(kPipe64, pairs(k64, 90, 60));
+  take(kTile128, pairs(k128, 178, 110));
+  if (!gelu) take(kPipe128, pairs(k128, 176, 120));
+  take(kPipe128x192, pairs(k192, gelu ? 240 : 230, 180));
+  if (tiles(128, 288) <= kCUs) take(kTile128x288, 220);
+  if (gelu && tiles(256, 192) <= kCUs) take(kTile256x192, 230);
+  return best;
+}
+
+// fp32 tiles: 64 x 64 (0) where it gives at least two workgroups per CU, 32 x 32 (1) below,
+// where it spreads the rows over more of the chip. All tiles sum K in one order.
+inline int choose_gemm_f32_tile(int M, int N) {
+  return (((long)M + 63) / 64) * (((long)N + 63) / 64) >= 512 ? 0 : 1;
+}
+
 // Row whose addresses an epilogue item reads when its own row m lies outside the matrix of M
 // rows (or its column outside the tile): its loads are unconditional, so they need a row that
 // exists. m0 is the first row of the item's pass over the tile, itself past the end where

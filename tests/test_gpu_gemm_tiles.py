@@ -13,28 +13,34 @@ from gpu_util import dev, host  # noqa: E402
 from helpers import TOL_BF16, rel_l2  # noqa: E402
 from paper_2511_22009_amd import Model, Precision  # noqa: E402
 
-# (width, heads, MLP width, latent H, W, rows) and the tiles of the batch
+# (width, heads, MLP width, latent H, W, rows); the tiles that the batch's QKV, output, up- and
+# down-projection take (a CPU test holds the rule to them); a row alone takes kPipe64, and
+# kHalf64 where the sums over K go in halves
 CASES = {
-    # QKV 1536: 128 x 128, fragments ahead; output and down-projection 512: 128 x 128 with both
-    # halves in a wavefront, K 512 and 520; up-projection 520: 128 x 128, register-staged
-    "w512": (512, 8, 520, 26, 30, 64),
-    # QKV 3480 and up-projection 3080: 256 x 192, K 1160, the second register-staged; output 1160: 128 x 128 registers
-    "w1160": (1160, 29, 3080, 26, 30, 16),
-    # up-projection 7000: 128 x 192, K 200; the others 64 x 64, the last with K 7000
-    "mlp7000": (200, 5, 7000, 26, 30, 8),
-    # output and down-projection 384: 128 x 192 with both halves in a wavefront (K 384, 776),
-    # QKV 1152: 128 x 192; 748 tokens: v leaves in groups of four tokens
-    "w384": (384, 6, 776, 44, 68, 64),
-    # QKV 2280: 128 x 288 (4095 rows, 195 tokens, K 760)
-    "w760": (760, 19, 520, 26, 30, 21),
-    # output and down-projection 640: 128 x 128 with the halves over two wavefronts
-    "w640": (640, 10, 640, 16, 24, 64),
+    # K 512 and 520
+    "w512": (512, 8, 520, 26, 30, 64, "kPipe128x192 kPipeHalf128 kTile128 kPipeHalf128"),
+    # K 1160 and 3080
+    "w1160": (1160, 29, 3080, 26, 30, 16, "kPipe128x192 kTile128 kTile256x192 kTile128"),
+    # K 200 and 7000
+    "mlp7000": (200, 5, 7000, 26, 30, 8, "kPipe64 kPipe64 kPipe128x192 kPipe64"),
+    # K 384 and 776; 748 tokens: v leaves in groups of four tokens
+    "w384": (384, 6, 776, 44, 68, 64, "kPipe128x192 kPipeHalf128x192 kPipe128x192 kPipeHalf128x192"),
+    # 4095 rows of 195 tokens, K 760
+    "w760": (760, 19, 520, 26, 30, 21, "kTile128x288 kTile128 kTile128 kTile128"),
+    # K 640
+    "w640": (640, 10, 640, 16, 24, 64, "kPipe128x192 kHalf128 kHalf128 kHalf128"),
+    # 5070 rows, K 480 and 776
+    "w480": (480, 10, 776, 26, 30, 26, "kPipe128 kHalf128x96 kTile128 kHalf128x96"),
+    # 6825 rows, K 840 and 1160
+    "w840": (840, 35, 1160, 26, 30, 35, "kPipe128x192 kPipe128 kTile256x192 kPipe128"),
+    # 7800 rows, K 1128 and 520
+    "w1128": (1128, 47, 520, 26, 30, 40, "kPipe128x192 kTile128x288 kTile128 kTile128x288"),
 }
 
 
 @pytest.mark.parametrize("name", CASES)
 def test_projection_tiles(name):
-    D, heads, mlp, H, Wd, B = CASES[name]
+    D, heads, mlp, H, Wd, B, _ = CASES[name]
     cfg = W.Config(name, C=4, H=H, W=Wd, p=2, D=D, L=1, heads=heads, mlp=mlp)
     blob = W.make_blob(cfg, init="tsens")
     om = oracle.load_blob(blob)
