@@ -44,7 +44,7 @@ MI355X_HBM_GBS = 8000.0
 # --no-sequential --copy-calibration`, each scaled by what the same counter reads for a
 # plain 256 MiB elementwise copy (FETCH_SIZE x 2.000, WRITE_SIZE x 1.000). An entry holds
 # only for the kernel sources it was measured on (hash below); otherwise traffic is null.
-KERNEL_SOURCES = ("k_gemm.hip", "k_attn.hip", "sf_device.h", "sf_launch.h")
+KERNEL_SOURCES = ("k_gemm.hip", "k_attn.hip", "sf_device.h", "sf_launch.h", "sf_rules.h")
 TRAFFIC = {
     ("s512", "bf16", "FC2"): {"bytes": 94525086, "sources": "cac1cfd0c9deab6b",
                               "profile": "profiles/stream_step_s512_bf16_hbm_traffic.md"},

@@ -1048,7 +1048,8 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_dma72x2_kernel(AttnArgs a) {
 
 // ------------------------------------------------------------------ fp32
 // e^x for x <= 0 (or NaN) in fp32: x log2 e is split into its rounded product hi and the
-// remainder lo (from the fused product and the next bits of log2 e), so that
+// remainder lo (the error-free product by a fused multiply-add, Ogita, Rump and Oishi's
+// TwoProductFMA, plus the next bits of log2 e times x), so that
 // e^x = 2^hi (1 + lo ln 2) with the hardware's 2^hi (about 1 ulp). Below -200 the result
 // is zero either way; the select keeps lo finite there, for masked keys (-inf), and
 // leaves a NaN alone.
@@ -1061,8 +1062,7 @@ __device__ __forceinline__ float exp_neg(float x) {
   return __builtin_fmaf(e, lo * kLn2, e);
 }
 
-// fp32 attention on the matrix cores (v_mfma_f32_16x16x4_f32, exact fp32 products and
-// sums). A workgroup owns 64 queries of one (row, head), 16 per wavefront, and steps over
+// fp32 attention on the matrix cores (v_mfma_f32_16x16x4_f32, fp32 operands and sums). A workgroup owns 64 queries of one (row, head), 16 per wavefront, and steps over
 // 32 keys at a time:
 //  * scores transposed, S^T = K Q^T: lane (l16, g) (g = lane / 16) holds query l16 and
 //    keys 4 g .. 4 g + 3 of every 16-key block, so the softmax is lane-local but for two
@@ -1076,9 +1076,9 @@ __device__ __forceinline__ float exp_neg(float x) {
 //    bf16 kernels; dims past dh and keys past Nk read as zeros.
 // The matrix cores bound it (64 fp32 FLOP per cycle and SIMD): 16 queries per wavefront
 // need 32 B/clk of LDS reads per CU, and the small query block spreads short sequences
-// over the chip. 4 rows x 12 heads x 1024 tokens, head dim 64 (12.9 GFLOP): 117 us, 110
-// TFLOP/s of the 154 that a large fp32 matrix product reaches, against 6940 us with a
-// thread per query; 3 rows x 4 heads x 140 tokens, head dim 48: 9.0 against 775 us.
+// over the chip. 4 rows x 12 heads x 1024 tokens, head dim 64 (12.9 GFLOP): 119 us, 108
+// TFLOP/s of the 153 that a large fp32 matrix product reaches, against 6940 us with a
+// thread per query; 3 rows x 4 heads x 140 tokens, head dim 48: 8.6 against 775 us.
 // A query's sums depend on its row's keys only, in one fixed order.
 constexpr int kF32Keys = 32;  // keys per step
 constexpr int kF32Q = 64;     // queries per workgroup

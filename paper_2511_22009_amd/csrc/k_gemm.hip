@@ -10,12 +10,12 @@
 //            once (one context entry per network row).
 //
 // bf16 path: v_mfma_f32_32x32x16_bf16 on BM x BN workgroup tiles over 64-wide K slices
-// (table and choice at the end), each wavefront owning a 64x64, 64x96, 32x96 or 32x32
-// sub-tile. Operand slices reach LDS directly in a swizzled layout or, for one tile, through
-// registers into a padded one; fragment reads are free of bank conflicts in both. The MFMAs take the weight
-// fragment as the first operand, so each lane ends up holding four adjacent output
-// columns of one row, which the epilogues move in 8- and 16-byte pieces. fp32 path:
-// v_mfma_f32_16x16x4_f32 on directly staged tiles.
+// (table at the end, choice in sf_rules.h), each wavefront owning a 64x64, 64x96, 32x96 or
+// 32x32 sub-tile. Operand slices reach LDS directly in a swizzled layout or, for three tiles,
+// through registers into a padded one; fragment reads are free of bank conflicts in both. The
+// MFMAs take the weight fragment as the first operand, so each lane ends up holding four
+// adjacent output columns of one row, which the epilogues move in 8- and 16-byte pieces. fp32
+// path: v_mfma_f32_16x16x4_f32 on directly staged tiles.
 #include <cmath>
 
 #include "sf_device.h"
@@ -1130,7 +1130,7 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void gemm_bf16_pipe_kernel(Gemm
 
 // ------------------------------------------------------------------ fp32 / MFMA
 //
-// fp32 projections on v_mfma_f32_16x16x4_f32 (exact fp32 products and sums). Operand
+// fp32 projections on v_mfma_f32_16x16x4_f32 (fp32 operands and sums). Operand
 // slices of 32 columns go global -> LDS directly into a ring of three stages, two slices
 // ahead, in the layout of the bf16 kernel above (rows of eight 16-byte chunks, swizzled).
 // An MFMA contracts four values, one per lane group g = lane / 16; a lane reads whole
@@ -1146,8 +1146,8 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void gemm_bf16_pipe_kernel(Gemm
 // straight from registers (single stores for the transposed v, whose lanes hold adjacent
 // tokens). The matrix cores bound it: 64 FLOP per cycle and SIMD against 16 B/clk of
 // operand loads per CU for the 64 x 64 tile. 4096 x 768 x 3072: 152 us, 127 TFLOP/s of the
-// 154 that a large product reaches, against 396 us for a 64 x 64 tile of vector FMAs;
-// 420 x 192 x 768: 7.0 against 77 us.
+// 153 that a large product reaches, against 396 us for a 64 x 64 tile of vector FMAs;
+// 420 x 192 x 768: 8.1 against 77 us.
 template <EpiKind KIND>
 __device__ __forceinline__ void f32_epilogue4(const GemmArgs& a, int m, int n, const f32x4& acc) {
   const f32x4 b = *(const f32x4*)(a.bias + n);
@@ -1316,10 +1316,11 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_f32_kernel(GemmArgs a) {
 }
 
 // fp32 tiles (BM x BN, wave grid): 64 x 64 where it gives at least two workgroups per CU,
-// 32 x 32 below, where it spreads the rows over more of the chip (4096 x 3072 x 768: 158 us
-// with 64 x 64, 171 with 32 x 32; 1024 x 768 x 768: 18.9 and 15.1; 420 x 192 x 768: 17.3
-// and 7.0). 128 x 64 and 128 x 128 tiles were no faster (149 and 156 us for the first, 54
-// us for 4096 x 768 x 768 against 47).
+// 32 x 32 below, where it spreads the rows over more of the chip (4096 x 3072 x 768: 161 us
+// with 64 x 64, 170 with 32 x 32; 1024 x 768 x 768: 19.0 and 14.6; 420 x 192 x 768: 17.6
+// and 8.1; 1024 x 2304 x 768, 576 tiles, 43.6 and 37.8: the line costs that one). 128 x 64 and
+// 128 x 128 tiles, with one sum per output, were no faster (4096 x 768 x 768 54 us with the
+// first against 47).
 #define SF_GEMM_F32_TILES(X) \
   X(0, 64, 64, 2, 2)         \
   X(1, 32, 32, 2, 2)
