@@ -308,7 +308,7 @@ __device__ __forceinline__ void bf16_epilogue(const GemmArgs& a, const f32x16 (&
         int which, r;
         qkv_dest<KIND>(a, part, r0, which, r);
         if (which < 2) continue;
-        if (tok + 16 <= a.ntok && m + 16 <= a.M && (tok & 15) == 0 && n + 8 <= a.N) {
+        if (tok + 16 <= a.ntok && m + 16 <= a.M && (tok & 15) == 0) {
           u32x4 rows[16];
 #pragma unroll
           for (int e = 0; e < 16; ++e) rows[e] = *(const u32x4*)&Cs[(rb * 16 + e) * CPB + cg * 8];
@@ -322,41 +322,44 @@ __device__ __forceinline__ void bf16_epilogue(const GemmArgs& a, const f32x16 (&
             *(u32x4*)(vt + (size_t)j * a.ldv) = u32x4{pk(0, 1), pk(2, 3), pk(8, 9), pk(10, 11)};
             *(u32x4*)(vt + (size_t)j * a.ldv + 8) = u32x4{pk(4, 5), pk(6, 7), pk(12, 13), pk(14, 15)};
           }
-        } else if ((a.ntok & 3) == 0 && n + 8 <= a.N) {
-          // token counts that are multiples of 4 but not of 16 (2760 x 2304 x 768 with 920
-          // tokens: 33.9 us with single stores, 20.7 so): four rows from m = 4 i on
-          // are four tokens of one network row from a multiple of 4 on, which the permuted
-          // order keeps adjacent: one 8-byte store per column
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int me = m + 4 * q;
-            if (me >= a.M) break;
-            const int re0 = (int)fdiv((uint32_t)me, a.div_ntok);
-            const int te = me - re0 * a.ntok;
-            int we, re;
-            qkv_dest<KIND>(a, part, re0, we, re);
-            u32x4 rows[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) rows[e] = *(const u32x4*)&Cs[(rb * 16 + 4 * q + e) * CPB + cg * 8];
-            bf16* vt = (bf16*)a.vT + (((size_t)re * a.heads + head) * a.dh + d0) * a.ldv + vt_pos(te);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-              const uint32_t sel = (j & 1) ? 0x07060302u : 0x05040100u;
-              const uint2 w = {__builtin_amdgcn_perm(rows[1][j >> 1], rows[0][j >> 1], sel),
-                               __builtin_amdgcn_perm(rows[3][j >> 1], rows[2][j >> 1], sel)};
-              *(uint2*)(vt + (size_t)j * a.ldv) = w;
-            }
-          }
         } else {
-          for (int e = 0; e < 16 && m + e < a.M; ++e) {
-            const int me = m + e;
-            const int re0 = (int)fdiv((uint32_t)me, a.div_ntok);
-            const int te = me - re0 * a.ntok;
+          // Other rows: four tokens of a network row from a multiple of 4 on stay adjacent in
+          // the permuted order and leave as one 8-byte store per column, by the item that
+          // holds the first of them (the others may lie in the next item, not in the next
+          // tile). Tokens of a group that the tile or the network row holds in part go singly.
+          // Single stores for every token count that is no multiple of 4 bounded the launch:
+          // at 2058 tokens 4116 x 1008 x 336 25.6 us with them and 14.2 so, 8232 x 2880 x 960
+          // 82.2 and 57.8.
+          const int m_end = min(m0 + BM, a.M);
+          int r0e = r0, te = tok;
+          for (int e = 0; e < 16 && m + e < m_end;) {
+            const int q = te & 3, first = m + e - q;
+            const bool whole = first >= m0 && first + 4 <= m_end && te - q + 4 <= a.ntok;
+            const int step = whole ? 4 - q : 1;
             int we, re;
-            qkv_dest<KIND>(a, part, re0, we, re);
-            for (int j = 0; j < 8 && n + j < a.N; ++j)
-              ((bf16*)a.vT)[(((size_t)re * a.heads + head) * a.dh + d0 + j) * a.ldv + vt_pos(te)] =
-                  Cs[(rb * 16 + e) * CPB + cg * 8 + j];
+            qkv_dest<KIND>(a, part, r0e, we, re);
+            bf16* vt = (bf16*)a.vT + (((size_t)re * a.heads + head) * a.dh + d0) * a.ldv + vt_pos(te);
+            const bf16* cp = Cs + (rb * 16 + e) * CPB + cg * 8;
+            if (!whole) {
+              for (int j = 0; j < 8; ++j) vt[(size_t)j * a.ldv] = cp[j];
+            } else if (q == 0) {
+              u32x4 rows[4];
+#pragma unroll
+              for (int u = 0; u < 4; ++u) rows[u] = *(const u32x4*)&cp[u * CPB];
+#pragma unroll
+              for (int j = 0; j < 8; ++j) {
+                const uint32_t sel = (j & 1) ? 0x07060302u : 0x05040100u;
+                const uint2 w = {__builtin_amdgcn_perm(rows[1][j >> 1], rows[0][j >> 1], sel),
+                                 __builtin_amdgcn_perm(rows[3][j >> 1], rows[2][j >> 1], sel)};
+                *(uint2*)(vt + (size_t)j * a.ldv) = w;
+              }
+            }
+            e += step;
+            te += step;
+            if (te >= a.ntok) {
+              te = 0;
+              ++r0e;
+            }
           }
         }
       }

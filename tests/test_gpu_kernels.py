@@ -74,6 +74,38 @@ def test_block0_intermediates(name, prec):
         assert worst[key] <= TOL[prec], worst
 
 
+@pytest.mark.parametrize("D,heads", [(192, 4), (336, 6)], ids=["dh48", "dh56"])
+@pytest.mark.parametrize("gh,gw", [(1, 1), (1, 3), (1, 5), (3, 5), (3, 7), (5, 6), (7, 9), (5, 13), (9, 22), (21, 25)])
+def test_transposed_values_of_any_token_count(gh, gw, D, heads):
+    """The transposed values that the QKV projection leaves, where token counts are no
+    multiples of 4 or 16: groups of four tokens start at any row of a tile, reach from one
+    group of 16 rows into the next, and are cut by tiles and network rows. Every row of a
+    batch holds the bits it has alone, the columns of keys past the last stay zero, and a
+    row agrees with the oracle."""
+    from paper_2511_22009_amd import Model, Precision
+    B = 7
+    cfg = W.Config("vt", C=4, H=2 * gh, W=2 * gw, p=2, D=D, L=1, heads=heads, mlp=64, K=1, schedule="uniform1")
+    blob = W.make_blob(cfg, init="tsens")
+    m = Model(blob, Precision.BF16, B)
+    x = W.latents(cfg, B, seed=61)
+    t = np.random.default_rng(62).uniform(0.0, 1.0, B).astype(np.float32)
+    shape = (heads, D // heads, m.info["vt_ld"])
+    tok = np.arange(cfg.N)
+    col = (tok & ~12) | ((tok & 4) << 1) | ((tok & 8) >> 1)
+    past = np.setdiff1d(np.arange(shape[2]), col)
+    m.residual(dev(x), t, 1)
+    batch = host(m.debug_read(Buffer.VT, (B,) + shape))
+    assert (batch[..., past] == 0).all()
+    for k in range(B):
+        m.residual(dev(x[k:k + 1]), t[k:k + 1], 1)
+        np.testing.assert_array_equal(host(m.debug_read(Buffer.VT, (1,) + shape))[0], batch[k])
+    tr = {}
+    oracle.residual_one(oracle.load_blob(blob), x[B - 1], t[B - 1], None, 1, trace=tr)
+    v = batch[B - 1][..., col].transpose(2, 0, 1).reshape(cfg.N, D)
+    assert rel_l2(v, tr["v"]) <= TOL["bf16"]
+    m.close()
+
+
 @pytest.mark.parametrize("HW", [(32, 64), (10, 12), (8, 8)], ids=["512tok", "30tok", "16tok"])
 @pytest.mark.parametrize("D,heads", [(128, 2), (144, 2), (96, 2), (64, 2), (48, 2), (208, 2), (240, 2), (256, 2)],
                          ids=["dh64", "dh72", "dh48", "dh32", "dh24", "dh104", "dh120", "dh128"])
