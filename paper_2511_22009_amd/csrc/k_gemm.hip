@@ -1407,7 +1407,7 @@ static hipError_t launch_f32_tile(int tile, const GemmArgs& a, hipStream_t s) {
 
 template <EpiKind KIND>
 static hipError_t launch_kind(bool use_bf16, const GemmArgs& a, hipStream_t s) {
-  if (use_bf16) return launch_bf16_tile<KIND>(choose_gemm_tile(a.M, a.N, KIND), a, s);
+  if (use_bf16) return launch_bf16_tile<KIND>(choose_gemm_tile(a.M, a.N, a.K, a.ntok, KIND), a, s);
   return launch_f32_tile<KIND>(choose_gemm_f32_tile(a.M, a.N), a, s);
 }
 

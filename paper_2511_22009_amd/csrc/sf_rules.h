@@ -36,18 +36,30 @@ constexpr bool gemm_tile_used(GemmTile tile, EpiKind kind) {
   return tile == kTile256x192 ? kind == EPI_GELU : tile != kPipe128 || kind != EPI_GELU;
 }
 
+// What a pair of workgroups of a tile costs that a CU runs side by side, in about ns: so much
+// per 64-wide slice of K, and so much once, by what the epilogue does (residual, QKV of whole
+// groups of 16 tokens, QKV of other token counts, GELU). `alone` is what a last one that has
+// the CU for itself takes of that, in percent.
+struct TileCost {
+  GemmTile tile;
+  int bm, bn, slice, alone;
+  int once[4];
+};
+
 // Which tile: the one with the least work on its busiest CU. A CU gets k = tiles / 256 of
-// them, rounded up. A tile whose LDS leaves room for one workgroup per CU costs a fixed
-// amount each; of the smaller ones two run side by side, so they cost so much per pair and,
-// where k is odd, a last one that has the CU for itself. That last one is dear where only the
-// other workgroup hides the loads: 128 x 128 with the fragments ahead takes 0.85 to 0.98 of
-// the register-staged one's time at even k and 1.03 to 1.24 at odd k.
+// them, rounded up. Two run side by side, so they cost so much per pair and, where k is odd, a
+// last one. That one is dear where only the other workgroup hides the loads: 128 x 128 with the
+// fragments ahead takes 0.85 to 0.98 of the register-staged one's time at even k and 1.03 to
+// 1.24 at odd k. (Where the LDS leaves room for one workgroup per CU `alone` is near 50.)
+// The share that does not grow with K is twice as large for 128 x 192 as for 128 x 128, so
+// below about ten slices the register-staged 128 x 128 wins where their work over K is level.
 //
-// Costs are relative, fitted to launches of all four projections of one-block networks: 22
-// widths from 64 to 2048 (N to 8192, K to 8192) at 256 to 16384 rows, 968 of them. The rule's
-// choice takes 1.004 of the fastest tile's time on average, 1.2 in the worst case; choosing by
-// k alone and by a threshold for the short ones took 1.021 and 1.6. Some times (us per
-// launch, rows x N x K):
+// The costs are fitted to launches of all four projections of one-block networks, 3832 of
+// them: 25 widths from 192 to 2048, K from 192 to 8192, at 256 to 26754 rows of 256, 1023
+// and 2058 tokens. The rule's choice takes 1.003 of the fastest tile's time on average, 1.19
+// in the worst case; without K and the kind of epilogue it took 1.007, most of it at the two odd
+// token counts (QKV 1.017). 128 x 128 throughout (outputs summed in one go) takes 1.095. Some
+// times (us per launch, rows x N x K):
 //   * 64 x 64: 2048 x 1024 x 4096 26.6, the next best 34.8 (128 x 128); 2048 x 896 x 896 11.8
 //     and 15.3; 1024 x 2304 x 768, more than two per CU, 13.1 and 11.1.
 //   * 128 x 128, register-staged, against fragments ahead: 12288 x 1024 x 4096 (k = 3) 107.6
@@ -68,36 +80,42 @@ constexpr bool gemm_tile_used(GemmTile tile, EpiKind kind) {
 //     split); 128 x 192 with both halves in a wavefront 8192 x 768 x 768 21.6 and, 128 x 96,
 //     23.2, but 12288 x 768 x 768 (1.5 rounds of it) 33.8 and 32.2; 128 x 128 12288 x 576 x 576
 //     21.7 with both halves in a wavefront, 22.8 split, 25.5 with 128 x 96, 29.8 with 128 x 192.
-inline GemmTile choose_gemm_tile(int M, int N, EpiKind kind) {
+inline GemmTile choose_gemm_tile(int M, int N, int K, int ntok, EpiKind kind) {
   constexpr long kCUs = 256;
-  auto tiles = [&](int bm, int bn) { return ((long)M + bm - 1) / bm * (((long)N + bn - 1) / bn); };
-  auto most = [&](int bm, int bn) { return (tiles(bm, bn) + kCUs - 1) / kCUs; };
-  auto pairs = [](long k, long pair, long last) { return k / 2 * pair + k % 2 * last; };
-  long cost = -1;
+  constexpr TileCost kHalves[] = {{kHalf64, 64, 64, 696, 58, {1052, 1052, 1052, 1052}},
+                                  {kHalf128x96, 128, 96, 1852, 50, {2883, 2883, 2883, 2883}},
+                                  {kHalf128, 128, 128, 1950, 54, {4247, 4247, 4247, 4247}},
+                                  {kPipeHalf128x192, 128, 192, 2933, 51, {3557, 3557, 3557, 3557}},
+                                  {kPipeHalf128, 128, 128, 1530, 97, {3266, 3266, 3266, 3266}}};
+  constexpr TileCost kWhole[] = {{kPipe64, 64, 64, 640, 69, {861, 1915, 2171, 1299}},
+                                 {kTile128, 128, 128, 1303, 59, {2126, 2573, 2614, 1921}},
+                                 {kPipe128, 128, 128, 1249, 88, {2640, 2842, 3187, 2542}},
+                                 {kPipe128x192, 128, 192, 1636, 76, {5692, 4018, 4433, 4841}},
+                                 {kTile128x288, 128, 288, 1565, 94, {2655, 2962, 2476, 2639}},
+                                 {kTile256x192, 256, 192, 1570, 100, {4650, 4650, 4650, 4650}}};
+  const bool halves = sums_halves(N);
+  const int epi = kind == EPI_GELU ? 3 : kind == EPI_QKV || kind == EPI_KVX ? 1 + (ntok % 16 != 0) : 0;
+  const long slices = ((long)K + 63) / 64;
+  long least = -1;
   GemmTile best = kTile128;
-  auto take = [&](GemmTile tile, long c) {
-    if (cost < 0 || c < cost) {
-      best = tile;
-      cost = c;
+  auto take = [&](const TileCost& t) {
+    if (!gemm_tile_used(t.tile, kind)) return;
+    const long tiles = ((long)M + t.bm - 1) / t.bm * (((long)N + t.bn - 1) / t.bn);
+    const long k = (tiles + kCUs - 1) / kCUs;
+    // one per CU by its LDS (its costs are one workgroup's), and only where one round of it holds
+    // everything: slower than pairs of smaller ones beyond
+    if ((t.tile == kTile128x288 || t.tile == kTile256x192) && k > 1) return;
+    const long pair = t.slice * slices + t.once[epi];
+    const long cost = k / 2 * pair * 100 + k % 2 * pair * t.alone;
+    if (least < 0 || cost < least) {
+      best = t.tile;
+      least = cost;
     }
   };
-  const long k64 = most(64, 64), k128 = most(128, 128), k192 = most(128, 192);
-  if (sums_halves(N)) {
-    if (tiles(64, 64) <= 2 * kCUs) return kHalf64;
-    take(kHalf64, pairs(k64, 121, 74));
-    take(kHalf128x96, 100 * most(128, 96));
-    take(kPipeHalf128x192, 156 * k192);
-    take(kHalf128, 125 * k128);
-    take(kPipeHalf128, pairs(k128, 190, 126));
-    return best;
-  }
-  const bool gelu = kind == EPI_GELU;
-  take(kPipe64, pairs(k64, 90, 60));
-  take(kTile128, pairs(k128, 178, 110));
-  if (!gelu) take(kPipe128, pairs(k128, 176, 120));
-  take(kPipe128x192, pairs(k192, gelu ? 240 : 230, 180));
-  if (tiles(128, 288) <= kCUs) take(kTile128x288, 220);
-  if (gelu && tiles(256, 192) <= kCUs) take(kTile256x192, 230);
+  if (halves)
+    for (const TileCost& t : kHalves) take(t);
+  else
+    for (const TileCost& t : kWhole) take(t);
   return best;
 }
 

@@ -18,23 +18,27 @@ from paper_2511_22009_amd import Model, Precision  # noqa: E402
 # kHalf64 where the sums over K go in halves
 CASES = {
     # K 512 and 520
-    "w512": (512, 8, 520, 26, 30, 64, "kPipe128x192 kPipeHalf128 kTile128 kPipeHalf128"),
+    "w512": (512, 8, 520, 26, 30, 64, "kTile128 kPipeHalf128 kTile128 kPipeHalf128"),
     # K 1160 and 3080
     "w1160": (1160, 29, 3080, 26, 30, 16, "kPipe128x192 kTile128 kTile256x192 kTile128"),
     # K 200 and 7000
-    "mlp7000": (200, 5, 7000, 26, 30, 8, "kPipe64 kPipe64 kPipe128x192 kPipe64"),
+    "mlp7000": (200, 5, 7000, 26, 30, 8, "kPipe64 kPipe64 kTile128 kPipe64"),
     # K 384 and 776; 748 tokens: v leaves in groups of four tokens
-    "w384": (384, 6, 776, 44, 68, 64, "kPipe128x192 kPipeHalf128x192 kPipe128x192 kPipeHalf128x192"),
+    "w384": (384, 6, 776, 44, 68, 64, "kPipe128x192 kPipeHalf128x192 kTile128 kPipeHalf128x192"),
     # 4095 rows of 195 tokens, K 760
     "w760": (760, 19, 520, 26, 30, 21, "kTile128x288 kTile128 kTile128 kTile128"),
     # K 640
     "w640": (640, 10, 640, 16, 24, 64, "kPipe128x192 kHalf128 kHalf128 kHalf128"),
     # 5070 rows, K 480 and 776
-    "w480": (480, 10, 776, 26, 30, 26, "kPipe128 kHalf128x96 kTile128 kHalf128x96"),
+    "w480": (480, 10, 776, 26, 30, 26, "kTile128 kHalf128x96 kTile128 kHalf128x96"),
     # 6825 rows, K 840 and 1160
     "w840": (840, 35, 1160, 26, 30, 35, "kPipe128x192 kPipe128 kTile256x192 kPipe128"),
     # 7800 rows, K 1128 and 520
     "w1128": (1128, 47, 520, 26, 30, 40, "kPipe128x192 kTile128x288 kTile128 kTile128x288"),
+    # 2145 rows, K 648 and 776
+    "w648": (648, 27, 776, 26, 30, 11, "kPipe128 kPipe64 kPipe64 kPipe64"),
+    # 8190 rows, K 552 and 3064
+    "w552": (552, 23, 3064, 26, 30, 42, "kTile128 kTile128 kPipe128x192 kPipe128"),
 }
 
 

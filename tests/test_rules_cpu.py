@@ -127,10 +127,10 @@ TILES = r"""
 int main(int argc, char** argv) {  // M N kind ...: the tile of each, and whether it is compiled for that kind
   const char* const names[] = {"kTile128", "kTile128x288", "kTile256x192", "kHalf128x96", "kHalf128", "kHalf64",
                                "kPipe128x192", "kPipe128", "kPipe64", "kPipeHalf128x192", "kPipeHalf128"};
-  for (int i = 1; i + 2 < argc; i += 3) {
-    const int N = std::atoi(argv[i + 1]);
-    const auto kind = (sf::EpiKind)std::atoi(argv[i + 2]);
-    const sf::GemmTile t = sf::choose_gemm_tile(std::atoi(argv[i]), N, kind);
+  for (int i = 1; i + 4 < argc; i += 5) {
+    const auto kind = (sf::EpiKind)std::atoi(argv[i + 4]);
+    const sf::GemmTile t = sf::choose_gemm_tile(std::atoi(argv[i]), std::atoi(argv[i + 1]), std::atoi(argv[i + 2]),
+                                                std::atoi(argv[i + 3]), kind);
     std::printf("%s %d\n", names[t], (int)sf::gemm_tile_used(t, kind));
   }
   return 0;
@@ -140,7 +140,7 @@ KINDS = {"QKV": 0, "RES_GATE": 1, "GELU": 2, "RES": 3, "RES_GATE_MLP": 4, "KVX":
 
 
 def _chosen(exe, asked):
-    args = [str(v) for M, N, kind in asked for v in (M, N, KINDS[kind])]
+    args = [str(v) for M, N, K, ntok, kind in asked for v in (M, N, K, ntok, KINDS[kind])]
     out = subprocess.run([exe] + args, capture_output=True, text=True, timeout=60, check=True).stdout.split()
     return out[0::2], out[1::2]
 
@@ -152,11 +152,13 @@ def test_tiles_of_the_projection_cases(tmp_path_factory):
     exe = _compiled(tmp_path_factory, "tiles", TILES)
     seen = set()
     for D, _, mlp, H, Wd, B, want in CASES.values():
-        shapes = [(3 * D, "QKV"), (D, "RES_GATE"), (mlp, "GELU"), (D, "RES_GATE_MLP")]
+        shapes = [(3 * D, D, "QKV"), (D, D, "RES_GATE"), (mlp, D, "GELU"), (D, mlp, "RES_GATE_MLP")]
+        ntok = (H // 2) * (Wd // 2)
         for rows in (B, 1):
-            tiles, _ = _chosen(exe, [(rows * (H // 2) * (Wd // 2), N, kind) for N, kind in shapes])
+            tiles, _ = _chosen(exe, [(rows * ntok, N, K, ntok, kind) for N, K, kind in shapes])
             if rows == 1:
-                want = " ".join("kHalf64" if N <= 768 and (N % 96 == 0 or N % 128 == 0) else "kPipe64" for N, _ in shapes)
+                want = " ".join("kHalf64" if N <= 768 and (N % 96 == 0 or N % 128 == 0) else "kPipe64"
+                                for N, _, _ in shapes)
             assert tiles == want.split(), (D, rows)
             seen |= set(tiles)
     assert len(seen) == 11, seen
@@ -166,11 +168,12 @@ def test_every_tile_that_is_chosen_is_compiled(tmp_path_factory):
     """Over widths, rows and epilogues: a tile that the launcher has no kernel for is never
     chosen, and M never changes which of the two orders of sums a width gets."""
     exe = _compiled(tmp_path_factory, "tiles", TILES)
-    asked = [(M, N, kind) for N in list(range(8, 1600, 56)) + [96, 128, 384, 512, 640, 768, 2304, 3456, 6144, 8192]
-             for M in (1, 30, 195, 1024, 2760, 4095, 7800, 16384, 65536) for kind in KINDS]
+    asked = [(M, N, K, ntok, kind) for N in list(range(8, 1600, 56)) + [96, 128, 384, 512, 640, 768, 2304, 3456, 6144, 8192]
+             for M, ntok in ((1, 1), (30, 30), (195, 195), (1024, 1024), (2760, 920), (4095, 195), (7800, 195),
+                             (16384, 1024), (65536, 4096)) for K in (8, 768, 8192) for kind in KINDS]
     for i in range(0, len(asked), 2000):
         part = asked[i:i + 2000]
         tiles, used = _chosen(exe, part)
-        for (M, N, kind), tile, ok in zip(part, tiles, used):
-            assert ok == "1", (M, N, kind, tile)
-            assert ("Half" in tile) == (N <= 768 and (N % 96 == 0 or N % 128 == 0)), (M, N, kind, tile)
+        for (M, N, K, ntok, kind), tile, ok in zip(part, tiles, used):
+            assert ok == "1", (M, N, K, ntok, kind, tile)
+            assert ("Half" in tile) == (N <= 768 and (N % 96 == 0 or N % 128 == 0)), (M, N, K, ntok, kind, tile)
