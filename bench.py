@@ -46,19 +46,19 @@ MI355X_HBM_GBS = 8000.0
 # only for the kernel sources it was measured on (hash below); otherwise traffic is null.
 KERNEL_SOURCES = ("k_gemm.hip", "k_attn.hip", "sf_device.h", "sf_launch.h", "sf_rules.h")
 TRAFFIC = {
-    ("s512", "bf16", "FC2"): {"bytes": 94524813, "sources": "297b5469526f4cd5",
+    ("s512", "bf16", "FC2"): {"bytes": 94525138, "sources": "4039acb714674390",
                               "profile": "profiles/stream_step_s512_bf16_hbm_traffic.md"},
-    ("s512", "bf16", "FC1"): {"bytes": 59984501, "sources": "297b5469526f4cd5",
+    ("s512", "bf16", "FC1"): {"bytes": 59984651, "sources": "4039acb714674390",
                               "profile": "profiles/stream_step_s512_bf16_hbm_traffic.md"},
-    ("s512_large", "bf16", "FC2"): {"bytes": 160620223, "sources": "297b5469526f4cd5",
+    ("s512_large", "bf16", "FC2"): {"bytes": 160620107, "sources": "4039acb714674390",
                                     "profile": "profiles/stream_step_s512_large_bf16.md"},
-    ("s512_large", "bf16", "FC1"): {"bytes": 118293190, "sources": "297b5469526f4cd5",
+    ("s512_large", "bf16", "FC1"): {"bytes": 118296019, "sources": "4039acb714674390",
                                     "profile": "profiles/stream_step_s512_large_bf16.md"},
-    ("s512_cfg", "bf16", "FC2"): {"bytes": 277090799, "sources": "297b5469526f4cd5",
+    ("s512_cfg", "bf16", "FC2"): {"bytes": 277198112, "sources": "4039acb714674390",
                                   "profile": "profiles/stream_step_s512_cfg_bf16.md"},
-    ("s512_cfg", "bf16", "FC1"): {"bytes": 278834648, "sources": "297b5469526f4cd5",
+    ("s512_cfg", "bf16", "FC1"): {"bytes": 278328596, "sources": "4039acb714674390",
                                   "profile": "profiles/stream_step_s512_cfg_bf16.md"},
-    ("s1024", "bf16", "ATTN"): {"bytes": 161786082, "sources": "297b5469526f4cd5",
+    ("s1024", "bf16", "ATTN"): {"bytes": 161784128, "sources": "4039acb714674390",
                                 "profile": "profiles/stream_step_s1024_bf16.md"},
 }
 
